@@ -64,6 +64,42 @@ __device__ __forceinline__ void st8(uint8_t* base, uint32_t off, v2u v) {
   else *p = v;
 }
 
+// The same at any element (2-byte) address. gfx950 moves 16 bytes per lane from and to any byte address in
+// one instruction; lanes that cover a contiguous span cost one more cache line per instruction. A copy of
+// 4 GB from a source 2 bytes off ran at 6.51 TB/s, 4 or 8 bytes off at 6.62, to a destination 2 bytes off at
+// 6.66, aligned on both sides at 6.68 (each at its best residency from 8 per CU up), so no realignment in
+// registers is needed.
+typedef v4u v4u_any __attribute__((aligned(2)));
+typedef v2u v2u_any __attribute__((aligned(2)));
+
+template <bool NT>
+__device__ __forceinline__ v4u ld16_any(const uint8_t* base, uint32_t off) {
+  const auto* p = (const __attribute__((address_space(1))) v4u_any*)((const gu8*)base + off);
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
+template <bool NT>
+__device__ __forceinline__ void st16_any(uint8_t* base, uint32_t off, v4u v) {
+  auto* p = (__attribute__((address_space(1))) v4u_any*)((gu8*)base + off);
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+template <bool NT>
+__device__ __forceinline__ v2u ld8_any(const uint8_t* base, uint32_t off) {
+  const auto* p = (const __attribute__((address_space(1))) v2u_any*)((const gu8*)base + off);
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
+template <bool NT>
+__device__ __forceinline__ void st8_any(uint8_t* base, uint32_t off, v2u v) {
+  auto* p = (__attribute__((address_space(1))) v2u_any*)((gu8*)base + off);
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // fp32 bits -> bf16 bits: round to nearest, ties to even; a NaN keeps its sign and top payload bits and
 // gets the quiet bit (so that a NaN whose payload sits in the low half never turns into infinity).
 __device__ __forceinline__ uint32_t bf16_rne(uint32_t u) {
@@ -107,20 +143,6 @@ __device__ __forceinline__ v4u cook(const Raw<CVT>& r) {
     return v4u{r.a.x << 16, r.a.x & 0xffff0000u, r.a.y << 16, r.a.y & 0xffff0000u};
   } else {
     return r.a;
-  }
-}
-
-// Element-wise conversion of n destination elements (misaligned converting segments; rare).
-template <int NTH, int CVT>
-__device__ void wg_convert_elems(const uint8_t* s, uint8_t* d, uint32_t n) {
-  for (uint32_t i = threadIdx.x; i < n; i += NTH) {
-    if constexpr (CVT == CVT_F32_BF16) {
-      const uint32_t u = *(const __attribute__((address_space(1))) uint32_t*)((const gu8*)s + 4u * i);
-      *(__attribute__((address_space(1))) uint16_t*)((gu8*)d + 2u * i) = uint16_t(bf16_rne(u));
-    } else {
-      const uint32_t b = *(const __attribute__((address_space(1))) uint16_t*)((const gu8*)s + 2u * i);
-      *(__attribute__((address_space(1))) uint32_t*)((gu8*)d + 4u * i) = b << 16;
-    }
   }
 }
 
@@ -310,7 +332,6 @@ __device__ __forceinline__ void wg_copy_bytes(const uint8_t* s, uint8_t* d, uint
 #define EMU_BUCKET_TILE_THREADS 64
 #endif
 constexpr int kXcds = int(kXcdCount);  // workgroups are dealt to the XCDs round-robin
-constexpr int kGeneralUnroll = 2;  // byte-granular reshard segments (misaligned runs; rare)
 constexpr int kBucketUnroll = EMU_BUCKET_UNROLL;
 constexpr int kShiftUnroll = EMU_SHIFT_UNROLL;
 constexpr int kBucketTileVecs = EMU_BUCKET_TILE_VECS;  // vectors per thread per pass of k_buckets_tile
@@ -445,6 +466,97 @@ __device__ __forceinline__ void tile_rows_f32_bf16(const uint8_t* s, uint8_t* d,
   }
 }
 
+// Segments at any alignment: cnt units (any_unit_bytes destination bytes each) of rows of `run` bytes. A
+// row's units sit on a grid of the destination's addresses: unit c covers the row's bytes [x, x + unit) with
+// x = c * unit - (row address & gmask), cut to the row by moving the first and the last one inward. A unit
+// moved inward overlaps its neighbour, and both write the same bytes there, so every access is a whole unit:
+// no head or tail bytes, no read outside the row, and every other store is aligned. Units of the 128-byte
+// grid also keep a tile's ends on cache lines, so that two tiles share a line only at a row's ends.
+//
+// ROWS: the units are numbered row-major from r0 in row 0 (at s and d), rv per row; lo and hi, the range
+// of the first byte of a unit, are those of a row. Otherwise: one row's slice, lo and hi relative to s and
+// d and possibly below 0.
+//
+// Bound by HBM. Against a tile per row slice with byte heads and tails, bodies realigned in registers and
+// conversions element by element: a 12-layer decoder with odd widths (460 MB of bf16 shards, TP1 PP2 -> TP2)
+// 202 -> 150 us, its fp32 -> bf16 conversion 757 -> 221 us, the 8B set into buckets of 2^28 - 2 bytes and out
+// of them 12.8 -> 10.4 ms (64 GB moved).
+constexpr uint32_t kAnyBias = 256;  // keeps the lanes' unsigned offsets from the base above 0
+
+template <int CVT>
+constexpr uint32_t any_src(uint32_t n) {  // source bytes behind n destination bytes
+  return CVT == CVT_F32_BF16 ? n * 2 : CVT == CVT_BF16_F32 ? n / 2 : n;
+}
+
+template <int U, bool NT, bool ZERO, int CVT, bool ROWS>
+__device__ __forceinline__ void tile_any(const uint8_t* s, uint8_t* d, uint32_t r0, uint32_t cnt, uint32_t rv,
+                                         uint32_t mg, uint32_t ss, uint32_t ds, uint32_t gmask, int32_t lo, int32_t hi) {
+  constexpr uint32_t D = ZERO ? 16u : any_unit_bytes(CVT);
+  constexpr int N = U * 16 / int(D), P = N > 8 ? 8 : N;  // units per lane, at most 8 of them in flight
+  const uint32_t tid = threadIdx.x, a0 = uint32_t(reinterpret_cast<uintptr_t>(d));
+  s = ZERO ? nullptr : s - any_src<CVT>(kAnyBias);
+  d -= kAnyBias;
+#pragma nounroll
+  for (uint32_t b = 0; b < cnt; b += uint32_t(kReshardThreads) * P) {  // one pass, two for a run's longer last tile
+    uint32_t to[P];
+    bool live[P];
+    v4u r[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const uint32_t i = b + k * kReshardThreads + tid, n = r0 + umin(i, cnt - 1);
+      const uint32_t q = !ROWS ? 0 : rv > 1 ? __umulhi(n, mg) : n;
+      const int32_t x = int32_t((n - q * rv) * D - ((a0 + q * ds) & gmask));
+      int32_t o = x < lo ? lo : x;
+      o = o > hi ? hi : o;
+      const uint32_t at = uint32_t(o) + kAnyBias;
+      live[k] = i < cnt && x < hi + int32_t(D) && x + int32_t(D) > lo;
+      to[k] = (ROWS ? q * ds : 0) + at;
+      const uint32_t from = (ROWS ? q * ss : 0) + any_src<CVT>(at);
+      if constexpr (ZERO) {
+        r[k] = v4u{0, 0, 0, 0};
+      } else if constexpr (CVT == CVT_BF16_F32) {
+        const v2u h = ld8_any<NT>(s, from);
+        r[k].x = h.x;
+        r[k].y = h.y;
+      } else {
+        r[k] = ld16_any<NT>(s, from);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      if (!live[k]) continue;
+      if constexpr (CVT == CVT_F32_BF16 && !ZERO) {
+        st8_any<NT>(d, to[k], to_bf16x4(r[k]));
+      } else if constexpr (CVT == CVT_BF16_F32 && !ZERO) {
+        st16_any<NT>(d, to[k], v4u{r[k].x << 16, r[k].x & 0xffff0000u, r[k].y << 16, r[k].y & 0xffff0000u});
+      } else {
+        st16_any<NT>(d, to[k], r[k]);
+      }
+    }
+  }
+}
+
+// Rows shorter than a unit (narrow column slices, the ends of bucket-cut rows): element by element, one per
+// lane and step, in row-major order.
+template <int U, bool ZERO, int CVT>
+__device__ void tile_elems(const DevSeg& g, uint64_t lt, const uint8_t* sb, uint8_t* db) {
+  typedef const __attribute__((address_space(1))) uint32_t* g32;
+  typedef const __attribute__((address_space(1))) uint16_t* g16;
+  constexpr uint32_t ES = CVT == CVT_BF16_F32 && !ZERO ? 4 : 2;
+  const uint64_t per = g.run / ES, total = g.rows * per;
+  for (uint32_t u = 0; u < U; ++u) {
+    const uint64_t e = lt * (uint64_t(kReshardThreads) * U) + u * kReshardThreads + threadIdx.x;
+    if (e >= total) return;
+    const uint64_t row = e / per, o = (e - row * per) * ES;
+    gu8* d = (gu8*)db + g.dst_off + row * g.dst_stride + o;
+    const gu8* s = (const gu8*)sb + g.src_off + row * g.src_stride;
+    if constexpr (ZERO) *(__attribute__((address_space(1))) uint16_t*)d = 0;
+    else if constexpr (CVT == CVT_F32_BF16) *(__attribute__((address_space(1))) uint16_t*)d = uint16_t(bf16_rne(*(g32)(s + o * 2)));
+    else if constexpr (CVT == CVT_BF16_F32) *(__attribute__((address_space(1))) uint32_t*)d = uint32_t(*(g16)(s + o / 2)) << 16;
+    else *(__attribute__((address_space(1))) uint16_t*)d = *(g16)(s + o);
+  }
+}
+
 template <int U, bool NT, bool ZERO, bool LDS, int CVT>
 __device__ __forceinline__ void run_tile(const DevSeg& g, uint64_t lt, const uint8_t* sb, uint8_t* db, v4u* stage) {
   constexpr uint64_t TV = uint64_t(kReshardThreads) * U;
@@ -485,20 +597,29 @@ __device__ __forceinline__ void run_tile(const DevSeg& g, uint64_t lt, const uin
     uint8_t* d = db + g.dst_off + row * g.dst_stride + v0 * 16;
     if constexpr (kHalves) tile_run_f32_bf16<U, NT>(s, d, cnt);
     else tile_run<U, NT, ZERO, LDS, CVT>(s, d, cnt, stage);
-  } else {  // SEG_GENERAL: misaligned runs, moved at a small unroll so that this rare path does not set
-            // the kernel's register budget
-    const uint64_t row = lt / g.param, ch = lt - row * g.param;
-    const uint64_t b0 = ch * TV * 16;
-    const uint32_t n = uint32_t(g.run - b0 < TV * 16 ? g.run - b0 : TV * 16);
+  } else if (mode == SEG_ANY_FLAT) {
+    constexpr uint32_t D = ZERO ? 16u : any_unit_bytes(CVT), TU = uint32_t(TV) * 16 / D;  // units per tile
+    const uint32_t n0 = uint32_t(lt) * TU, q0 = g.rv > 1 ? __umulhi(n0, g.magic) : n0;
+    tile_any<U, NT, ZERO, CVT, true>(ZERO ? nullptr : sb + g.src_off + uint64_t(q0) * g.src_stride,
+                                     db + g.dst_off + uint64_t(q0) * g.dst_stride, n0 - q0 * g.rv,
+                                     umin(g.param - n0, TU), g.rv, g.magic, uint32_t(g.src_stride),
+                                     uint32_t(g.dst_stride), g.mode >> SEG_GRID_SHIFT, 0, int32_t(g.run) - int32_t(D));
+  } else if (mode == SEG_ANY_CHUNK) {
+    // Slice ch of a row is its bytes [ch * TB - m, (ch + 1) * TB - m), cut to the row, with m the phase of the
+    // row's address on the grid; the last slice also takes what is left (up to gmask bytes).
+    constexpr uint32_t D = ZERO ? 16u : any_unit_bytes(CVT);
+    constexpr int32_t TB = int32_t(TV) * 16;
+    const uint32_t row = g.rows == 1 ? 0 : uint32_t(lt) / g.param, ch = uint32_t(lt) - row * g.param;
+    const uint64_t b0 = uint64_t(ch) * uint32_t(TB);
+    const uint8_t* s = ZERO ? nullptr : sb + g.src_off + row * g.src_stride + b0 / 16 * SV;
     uint8_t* d = db + g.dst_off + row * g.dst_stride + b0;
-    if constexpr (CVT == CVT_NONE || ZERO) {
-      wg_copy_bytes<kReshardThreads, kGeneralUnroll, kGeneralUnroll, NT, ZERO>(ZERO ? nullptr : sb + g.src_off + row * g.src_stride + b0,
-                                                              d, n);
-    } else {
-      constexpr uint32_t esd = CVT == CVT_F32_BF16 ? 2u : 4u;  // destination element bytes
-      constexpr uint32_t ess = CVT == CVT_F32_BF16 ? 4u : 2u;  // source element bytes
-      wg_convert_elems<kReshardThreads, CVT>(sb + g.src_off + row * g.src_stride + b0 / esd * ess, d, n / esd);
-    }
+    const uint32_t gmask = g.mode >> SEG_GRID_SHIFT;
+    const int32_t m = int32_t(uint32_t(reinterpret_cast<uintptr_t>(d)) & gmask);
+    const int32_t end = ch + 1 == g.param ? int32_t(g.run - b0) : TB - m;
+    tile_any<U, NT, ZERO, CVT, false>(s, d, 0, (uint32_t(end + m) + D - 1) / D, 0, 0, 0, 0, gmask, ch ? -m : 0,
+                                      end - int32_t(D));
+  } else {
+    tile_elems<U, ZERO, CVT>(g, lt, sb, db);
   }
 }
 

@@ -28,17 +28,25 @@ constexpr uint32_t kXcdCount = 8;          // XCDs of an MI355X; reshard grids a
 constexpr uint32_t kNoSeg = 0xffffffffu;   // tile map padding entry: the workgroup has no tile
 
 // Segment execution modes. Every "vec" mode needs src/dst offsets, strides and the run to be
-// multiples of 16 bytes (and 16-byte aligned tensor bases, an ABI requirement).
+// multiples of 16 bytes (and 16-byte aligned tensor bases, an ABI requirement); the "any" modes take
+// every other segment (offsets, strides and runs at any element).
 enum SegMode : uint32_t {
   SEG_VEC_1D = 0,        // one contiguous run; a tile is a fixed slice of it
   SEG_VEC_ROWS = 1,      // rows shorter than a tile; a tile is `param` whole rows
   SEG_VEC_ROWCHUNK = 2,  // rows longer than a tile; a tile is one slice of one row
-  SEG_GENERAL = 3,       // any byte alignment; a tile is one slice of one row, copied bytewise
+  SEG_ANY_FLAT = 3,      // as SEG_VEC_FLAT, in units placed on the destination's address grid (any_unit_bytes)
   SEG_VEC_FLAT = 4,      // rows of any length; a tile is a fixed slice of the rows' vectors in row-major
                          // order, so rows wrap inside a tile and only a segment's last tile is partial
+  SEG_ANY_CHUNK = 5,     // single runs and long rows: a tile is one slice of one row, cut on the same grid
+  SEG_ANY_ELEM = 6,      // runs shorter than a unit: element by element
 };
 constexpr uint32_t SEG_MODE_MASK = 0xff;
 constexpr uint32_t SEG_ZERO = 0x100;  // no source: write zeros
+constexpr uint32_t SEG_GRID_SHIFT = 16;  // mode >> 16: the grid of the "any" modes less one (15 or 127)
+
+// Destination bytes one lane moves at a time in the "any" modes: 16, or 8 when fp32 becomes bf16 (one
+// 16-byte source vector of four elements).
+constexpr uint32_t any_unit_bytes(int cvt) { return cvt == 1 ? 8u : 16u; }
 
 // Element conversion of a plan (all copy segments of one plan share it).
 enum Convert : int { CVT_NONE = 0, CVT_F32_BF16 = 1, CVT_BF16_F32 = 2 };
@@ -50,11 +58,10 @@ struct alignas(16) DevSeg {
   uint64_t rows, run;
   int32_t src_idx, dst_idx;
   uint32_t mode;   // SegMode | SEG_ZERO
-  uint32_t param;  // SEG_VEC_ROWS: rows per tile; SEG_VEC_ROWCHUNK / SEG_GENERAL: tiles per row;
-                   // SEG_VEC_FLAT: rows * rv, the segment's vectors
-  uint32_t rv;     // SEG_VEC_ROWS / SEG_VEC_FLAT: 16-byte vectors per row
-  uint32_t magic;  // SEG_VEC_ROWS / SEG_VEC_FLAT: ceil(2^32 / rv) for rv > 1 (n / rv == umulhi(n, magic)
-                   // for n * rv < 2^32)
+  uint32_t param;  // SEG_VEC_ROWS: rows per tile; SEG_VEC_ROWCHUNK / SEG_ANY_CHUNK: tiles per row;
+                   // SEG_VEC_FLAT / SEG_ANY_FLAT: rows * rv, the segment's vectors
+  uint32_t rv;     // SEG_VEC_ROWS / SEG_VEC_FLAT: 16-byte vectors per row; SEG_ANY_FLAT: units per row
+  uint32_t magic;  // with rv: ceil(2^32 / rv) for rv > 1 (n / rv == umulhi(n, magic) for n * rv < 2^32)
   uint64_t tile0;  // map index of the segment's first tile
 };
 static_assert(sizeof(DevSeg) == 80, "DevSeg layout");

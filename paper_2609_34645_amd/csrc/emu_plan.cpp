@@ -567,16 +567,18 @@ static void device_tables(const Plan& P, uint8_t* h) {
 }
 
 // Device segments, tiles and the workspace layout.
-// Whether a 2D vector segment can run as SEG_VEC_FLAT with tiles of TV vectors: the kernel finds the
-// row of vector n (n below rows * rv) as umulhi(n, ceil(2^32 / rv)), exact while n * rv < 2^32, and
-// keeps in-tile byte offsets in 31 bits: a tile spans at most 2 + TV / rv rows.
-static bool flat_ok(const emu_segment_t& g, uint64_t TV) {
-  const uint64_t rv = g.run / 16;
+// Whether a 2D segment of rv vectors (or units) per row can run in one row-major sequence with tiles of
+// TV of them: the kernel finds the row of vector n (n below rows * rv) as umulhi(n, ceil(2^32 / rv)), exact
+// while n * rv < 2^32, and keeps in-tile byte offsets in 31 bits: a tile spans at most 2 + TV / rv rows.
+static bool flat_ok(const emu_segment_t& g, uint64_t rv, uint64_t TV) {
   if (g.rows < 2 || rv == 0 || g.rows > 0xffffffffull) return false;
   if (rv > 0xffffffffull / rv || g.rows > 0xffffffffull / (rv * rv)) return false;  // rows * rv * rv < 2^32
   const uint64_t stride = std::max(g.src_stride, g.dst_stride);
   return stride < (1ull << 31) / (2 + TV / rv);
 }
+
+// ceil(2^32 / rv): the row of vector n is umulhi(n, magic) (see flat_ok).
+static uint32_t row_magic(uint64_t rv) { return rv > 1 ? uint32_t(((1ull << 32) + rv - 1) / rv) : 0u; }
 
 static int finalize(Plan& P) {
   const int U = P.tile_vecs;
@@ -590,6 +592,7 @@ static int finalize(Plan& P) {
   // source alignment the vector paths need: 16 bytes when each destination vector reads one or two
   // whole source vectors, 8 bytes when it reads half of one (bf16 -> fp32)
   const uint64_t salign = P.cvt == CVT_BF16_F32 ? 8 : 16;
+  const uint64_t esd = uint64_t(elem_size(P.side[1].lay.dtype));
   int32_t ngeneral = 0;
   const bool row_wrap = option(EMU_OPT_ROW_WRAP) != 0;
   for (size_t i = 0; i < P.segs.size(); ++i) {
@@ -604,20 +607,41 @@ static int finalize(Plan& P) {
                      (zero || (g.src_offset % salign == 0 && (g.rows == 1 || g.src_stride % salign == 0)));
     uint64_t nt;
     if (!vec) {
-      d.mode = SEG_GENERAL;
-      const uint64_t tpr = (g.run + TB - 1) / TB;
+      // A row's units sit on the destination's address grid: 128 bytes (a cache line) for rows of 2 KB and
+      // more, where the up to 15 units it adds to a row are few; 16 bytes for shorter rows. rv counts a
+      // row's units at the worst phase of its first byte. Rows run in one sequence only if that takes no
+      // more tiles than slices of single rows.
+      const uint64_t unit = zero ? 16 : any_unit_bytes(P.cvt);
+      const uint64_t grid = g.run >= 2048 ? 128 : 16;
+      const uint64_t rv0 = (g.run + grid - esd + unit - 1) / unit, per = grid / unit;
+      const uint64_t rv = grid == 128 ? (rv0 + per - 1) / per * per : rv0;
+      const uint64_t tpr = (g.run + TB - 1) / TB, units = TB / unit;
       if (tpr > 0xffffffffull) return fail(EMU_ERR_UNSUPPORTED, "row of %llu bytes too long", (unsigned long long)g.run);
-      d.param = uint32_t(tpr);
-      nt = g.rows * tpr;
+      d.mode = uint32_t(grid - 1) << SEG_GRID_SHIFT;
+      if (g.run < unit) {
+        const uint64_t es = P.cvt == CVT_BF16_F32 && !zero ? 4 : 2;  // bytes per lane and step
+        d.mode |= SEG_ANY_ELEM;
+        nt = (g.rows * (g.run / es) + TV - 1) / TV;
+      } else if (row_wrap && flat_ok(g, rv, units) && (g.rows * rv + units - 1) / units <= g.rows * tpr) {
+        d.mode |= SEG_ANY_FLAT;
+        d.rv = uint32_t(rv);
+        d.param = uint32_t(g.rows * rv);
+        d.magic = row_magic(rv);
+        nt = (d.param + units - 1) / units;
+      } else {
+        d.mode |= SEG_ANY_CHUNK;
+        d.param = uint32_t(tpr);
+        nt = g.rows * tpr;
+      }
       ++ngeneral;
     } else if (g.rows == 1) {
       d.mode = SEG_VEC_1D;
       nt = (g.run + TB - 1) / TB;
-    } else if (row_wrap && flat_ok(g, TV)) {
+    } else if (row_wrap && flat_ok(g, g.run / 16, TV)) {
       d.mode = SEG_VEC_FLAT;
       d.rv = uint32_t(g.run / 16);
       d.param = uint32_t(g.rows * d.rv);
-      d.magic = d.rv > 1 ? uint32_t(((1ull << 32) + d.rv - 1) / d.rv) : 0u;
+      d.magic = row_magic(d.rv);
       nt = (d.param + TV - 1) / TV;
     } else if (g.run <= TB) {
       d.mode = SEG_VEC_ROWS;
@@ -626,7 +650,7 @@ static int finalize(Plan& P) {
       const uint64_t stride = std::max(g.src_stride, g.dst_stride);
       const uint64_t by_offset = stride < (1ull << 31) ? ((1ull << 31) - g.run) / stride + 1 : 1;
       d.param = uint32_t(std::max<uint64_t>(1, std::min<uint64_t>(TB / g.run, by_offset)));
-      d.magic = d.rv > 1 ? uint32_t(((1ull << 32) + d.rv - 1) / d.rv) : 0u;
+      d.magic = row_magic(d.rv);
       nt = (g.rows + d.param - 1) / d.param;
     } else {
       d.mode = SEG_VEC_ROWCHUNK;
