@@ -186,9 +186,10 @@ typedef enum {
                                 threads per workgroup): 1, 2, 4, 8 or 16 (1 to 16 KB tiles), or 0 =
                                 automatic (default): 4 (4 KB tiles). Read by emu_plan, so a plan
                                 keeps its tile size */
-  EMU_OPT_XCD_REMAP = 1,     /* 1 = give each XCD one contiguous eighth of the reshard tiles instead of
+  EMU_OPT_XCD_REMAP = 1,     /* 1 = give each XCD whole blocks of consecutive reshard tiles instead of
                                 every eighth tile (default 1) */
-  EMU_OPT_NONTEMPORAL = 2,   /* 1 = streaming (non-temporal) loads and stores (default 1) */
+  EMU_OPT_NONTEMPORAL = 2,   /* 1 = streaming (non-temporal) loads and stores, written through to memory
+                                in large calls (default 1) */
   EMU_OPT_LDS_STAGING = 3,   /* 1 = stage each tile through LDS between load and store (default 0) */
   EMU_OPT_BUCKET_WG_PER_CU = 4, /* persistent pack/unpack grid: workgroups per compute unit (default 32) */
   EMU_OPT_BUCKET_TILES = 5,  /* 1 = pack/unpack with one workgroup per 4 KB stream chunk (upload-time
@@ -199,10 +200,11 @@ typedef enum {
                                 per compute unit, 1..32, enforced by reserving LDS per workgroup (the
                                 LDS is split in two halves, so odd caps above 1 round down to even);
                                 0 = no cap; -1 = automatic (default): 48 KB of reshard tiles (12 of
-                                4 KB, 6 of 8 KB), 40 KB for fp32 -> bf16 plans, 64 KB for bf16 ->
-                                fp32 plans, and 64 KB of pack/unpack chunks (16 of 4 KB); at least 2,
-                                no cap from 32 up. Bounds the bytes in flight per CU, which sets how
-                                well HBM serves a read/write stream */
+                                4 KB, 6 of 8 KB), for fp32 -> bf16 plans 24 KB, or 40 KB with
+                                misaligned runs, for large bf16 -> fp32 plans 56 KB, and 64 KB of
+                                pack/unpack chunks (16 of 4 KB); at least 2, no cap from 32 up.
+                                Bounds the bytes in flight per CU, which sets how well HBM serves a
+                                read/write stream */
   EMU_OPT_ROW_WRAP = 7       /* 1 = tile 2D segments as one row-major vector sequence, rows wrapping
                                 inside a tile, wherever the kernel's row arithmetic is exact (default);
                                 0 = whole rows per tile, or slices of one row. Read by emu_plan */

@@ -21,6 +21,7 @@ ARCH = "gfx950"
 # packed fp32 arithmetic is kept off for every HIP compile (no data arithmetic happens here anyway)
 HIP_FLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-Wall",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-mllvm", "-amdgpu-kernarg-preload-count=14",  # kernel arguments in registers at a wave's start
              f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}"]
 
 

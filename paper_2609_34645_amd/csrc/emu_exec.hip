@@ -31,18 +31,31 @@ typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v4u gv4u;
 typedef __attribute__((address_space(1))) uint8_t gu8;
 
-template <bool NT>
+// Cache policies of the kernels' loads and stores. POL_NT and POL_THROUGH load with "nt" (streaming).
+// POL_NT also stores with it; POL_THROUGH stores with "sc1 nt", as buffer stores: written through to memory
+// as they come, instead of staying in the XCD's L2 until evicted. With as many tiles in flight as the
+// reshard needs to cover its tables' latency, write-through holds HBM's read/write mix better: a bare
+// 4 KB-tile copy of 8 GB at 8 / 10 resident waves per CU ran at 6.71 / 6.55 TB/s against 6.52 / 6.28 with
+// "nt" (6.80 / 6.73 at 6), the 8B reshard at 10 per CU in 4.80 ms against 4.93. Each plan's choice is made
+// where it is launched.
+enum Policy : int { POL_PLAIN = 0, POL_NT = 1, POL_THROUGH = 2 };
+constexpr int kThroughBits = 2 | 16;  // nt | sc1
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t whole_range(uint8_t* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000);  // raw, unswizzled, 2^32 - 1 bytes
+}
+
+template <int POL>
 __device__ __forceinline__ v4u ld16(const uint8_t* base, uint32_t off) {
   const gv4u* p = (const gv4u*)((const gu8*)base + off);
-  if constexpr (NT) return __builtin_nontemporal_load(p);
+  if constexpr (POL != POL_PLAIN) return __builtin_nontemporal_load(p);
   else return *p;
 }
 
-template <bool NT>
+template <int POL>
 __device__ __forceinline__ void st16(uint8_t* base, uint32_t off, v4u v) {
-  gv4u* p = (gv4u*)((gu8*)base + off);
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
+  if constexpr (POL == POL_THROUGH) __builtin_amdgcn_raw_buffer_store_b128(v, whole_range(base), off, 0, kThroughBits);
+  else if constexpr (POL == POL_NT) __builtin_nontemporal_store(v, (gv4u*)((gu8*)base + off));
+  else *(gv4u*)((gu8*)base + off) = v;
 }
 
 __device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
@@ -50,18 +63,18 @@ __device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b 
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(1))) v2u gv2u;
 
-template <bool NT>
+template <int POL>
 __device__ __forceinline__ v2u ld8(const uint8_t* base, uint32_t off) {
   const gv2u* p = (const gv2u*)((const gu8*)base + off);
-  if constexpr (NT) return __builtin_nontemporal_load(p);
+  if constexpr (POL != POL_PLAIN) return __builtin_nontemporal_load(p);
   else return *p;
 }
 
-template <bool NT>
+template <int POL>
 __device__ __forceinline__ void st8(uint8_t* base, uint32_t off, v2u v) {
-  gv2u* p = (gv2u*)((gu8*)base + off);
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
+  if constexpr (POL == POL_THROUGH) __builtin_amdgcn_raw_buffer_store_b64(v, whole_range(base), off, 0, kThroughBits);
+  else if constexpr (POL == POL_NT) __builtin_nontemporal_store(v, (gv2u*)((gu8*)base + off));
+  else *(gv2u*)((gu8*)base + off) = v;
 }
 
 // The same at any element (2-byte) address. gfx950 moves 16 bytes per lane from and to any byte address in
@@ -72,31 +85,31 @@ __device__ __forceinline__ void st8(uint8_t* base, uint32_t off, v2u v) {
 typedef v4u v4u_any __attribute__((aligned(2)));
 typedef v2u v2u_any __attribute__((aligned(2)));
 
-template <bool NT>
+template <int POL>
 __device__ __forceinline__ v4u ld16_any(const uint8_t* base, uint32_t off) {
   const auto* p = (const __attribute__((address_space(1))) v4u_any*)((const gu8*)base + off);
-  if constexpr (NT) return __builtin_nontemporal_load(p);
+  if constexpr (POL != POL_PLAIN) return __builtin_nontemporal_load(p);
   else return *p;
 }
 
-template <bool NT>
+template <int POL>
 __device__ __forceinline__ void st16_any(uint8_t* base, uint32_t off, v4u v) {
   auto* p = (__attribute__((address_space(1))) v4u_any*)((gu8*)base + off);
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  if constexpr (POL != POL_PLAIN) __builtin_nontemporal_store(v, p);
   else *p = v;
 }
 
-template <bool NT>
+template <int POL>
 __device__ __forceinline__ v2u ld8_any(const uint8_t* base, uint32_t off) {
   const auto* p = (const __attribute__((address_space(1))) v2u_any*)((const gu8*)base + off);
-  if constexpr (NT) return __builtin_nontemporal_load(p);
+  if constexpr (POL != POL_PLAIN) return __builtin_nontemporal_load(p);
   else return *p;
 }
 
-template <bool NT>
+template <int POL>
 __device__ __forceinline__ void st8_any(uint8_t* base, uint32_t off, v2u v) {
   auto* p = (__attribute__((address_space(1))) v2u_any*)((gu8*)base + off);
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  if constexpr (POL != POL_PLAIN) __builtin_nontemporal_store(v, p);
   else *p = v;
 }
 
@@ -116,16 +129,16 @@ template <> struct Raw<CVT_BF16_F32> { v2u a; };
 template <int CVT>
 constexpr uint32_t kSrcVecBytes = CVT == CVT_F32_BF16 ? 32u : CVT == CVT_BF16_F32 ? 8u : 16u;
 
-template <int CVT, bool NT>
+template <int CVT, int POL>
 __device__ __forceinline__ Raw<CVT> ld_raw(const uint8_t* s, uint32_t off) {
   Raw<CVT> r;
   if constexpr (CVT == CVT_F32_BF16) {
-    r.a = ld16<NT>(s, off);
-    r.b = ld16<NT>(s, off + 16u);
+    r.a = ld16<POL>(s, off);
+    r.b = ld16<POL>(s, off + 16u);
   } else if constexpr (CVT == CVT_BF16_F32) {
-    r.a = ld8<NT>(s, off);
+    r.a = ld8<POL>(s, off);
   } else {
-    r.a = ld16<NT>(s, off);
+    r.a = ld16<POL>(s, off);
   }
   return r;
 }
@@ -151,6 +164,13 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(x >> 32));
   return (uint64_t(hi) << 32) | lo;
 }
+
+// Ends the wait for all loads of a tile at once. Ahead of stores that a lane mask guards: the compiler
+// counts loads and stores in one counter and cannot know which masked stores were issued, so without this
+// it waits for the tile's first stores to complete before it issues the last ones. A tile without masked
+// stores needs no such wait, which is why full tiles have paths of their own below. At 6 resident tiles per
+// CU the 1B TP4 -> TP2 reshard took 957 us with both, 1,086 us before; at 8 per CU 926 against 962.
+__device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
 
 // 16 bytes starting `sh` bytes (0 < sh < 16) into the 32-byte pair (lo, hi). Q = sh / 4 is a
 // template parameter so that the dword selection is static; the byte shift uses v_alignbyte.
@@ -351,9 +371,10 @@ __device__ __forceinline__ void stage_through_lds(v4u (&r)[U], v4u* stage) {
 }
 
 // Rows of rv vectors at strides ss and ds bytes from s and d, read in row-major vector order: the tile
-// holds vectors r0 .. r0 + last of that order. Vector n is in row n / rv (a multiply-high by the host's
-// magic number) at column n % rv; the host keeps every in-tile byte offset below 2^31.
-template <int U, bool NT, bool ZERO, bool LDS, int CVT>
+// holds vectors r0 .. r0 + last of that order (FULL: as many as the tile has). Vector n is in row n / rv (a
+// multiply-high by the host's magic number) at column n % rv; the host keeps every in-tile byte offset
+// below 2^31.
+template <int U, int POL, bool ZERO, bool LDS, int CVT, bool FULL>
 __device__ __forceinline__ void tile_rows(const uint8_t* s, uint8_t* d, uint32_t r0, uint32_t last, uint32_t rv,
                                           uint32_t mg, uint32_t ss, uint32_t ds, v4u* stage) {
   const uint32_t tid = threadIdx.x;
@@ -365,10 +386,11 @@ __device__ __forceinline__ void tile_rows(const uint8_t* s, uint8_t* d, uint32_t
     Raw<CVT> raw[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const uint32_t n = r0 + umin(u * kReshardThreads + tid, last);
+      const uint32_t i = u * kReshardThreads + tid, n = r0 + (FULL ? i : umin(i, last));
       const uint32_t q = rv > 1 ? __umulhi(n, mg) : n;
-      raw[u] = ld_raw<CVT, NT>(s, q * ss + (n - q * rv) * kSrcVecBytes<CVT>);
+      raw[u] = ld_raw<CVT, POL>(s, q * ss + (n - q * rv) * kSrcVecBytes<CVT>);
     }
+    if constexpr (!FULL) loads_done();
 #pragma unroll
     for (int u = 0; u < U; ++u) r[u] = cook<CVT>(raw[u]);
   }
@@ -378,12 +400,12 @@ __device__ __forceinline__ void tile_rows(const uint8_t* s, uint8_t* d, uint32_t
     const uint32_t i = u * kReshardThreads + tid;
     const uint32_t n = r0 + i;
     const uint32_t q = rv > 1 ? __umulhi(n, mg) : n;
-    if (i <= last) st16<NT>(d, q * ds + (n - q * rv) * 16u, r[u]);
+    if (FULL || i <= last) st16<POL>(d, q * ds + (n - q * rv) * 16u, r[u]);
   }
 }
 
-// A contiguous run of cnt (1 <= cnt <= kReshardThreads * U) destination vectors.
-template <int U, bool NT, bool ZERO, bool LDS, int CVT>
+// A contiguous run of cnt (1 <= cnt <= kReshardThreads * U) destination vectors (FULL: as many as the tile has).
+template <int U, int POL, bool ZERO, bool LDS, int CVT, bool FULL>
 __device__ __forceinline__ void tile_run(const uint8_t* s, uint8_t* d, uint32_t cnt, v4u* stage) {
   const uint32_t tid = threadIdx.x;
   const uint32_t last = cnt - 1;
@@ -394,7 +416,11 @@ __device__ __forceinline__ void tile_run(const uint8_t* s, uint8_t* d, uint32_t 
   } else {
     Raw<CVT> raw[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) raw[u] = ld_raw<CVT, NT>(s, umin(u * kReshardThreads + tid, last) * kSrcVecBytes<CVT>);
+    for (int u = 0; u < U; ++u) {
+      const uint32_t i = u * kReshardThreads + tid;
+      raw[u] = ld_raw<CVT, POL>(s, (FULL ? i : umin(i, last)) * kSrcVecBytes<CVT>);
+    }
+    if constexpr (!FULL) loads_done();
 #pragma unroll
     for (int u = 0; u < U; ++u) r[u] = cook<CVT>(raw[u]);
   }
@@ -402,7 +428,7 @@ __device__ __forceinline__ void tile_run(const uint8_t* s, uint8_t* d, uint32_t 
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const uint32_t i = u * kReshardThreads + tid;
-    if (i <= last) st16<NT>(d, i * 16u, r[u]);
+    if (FULL || i <= last) st16<POL>(d, i * 16u, r[u]);
   }
 }
 
@@ -420,7 +446,7 @@ __device__ __forceinline__ v2u to_bf16x4(v4u a) {
 template <int U>
 constexpr int kCvtPass = U > 8 ? 8 : U;
 
-template <int U, bool NT>
+template <int U, int POL, bool FULL>
 __device__ __forceinline__ void tile_run_f32_bf16(const uint8_t* s, uint8_t* d, uint32_t cnt) {
   constexpr int P = kCvtPass<U>;
   const uint32_t tid = threadIdx.x;
@@ -429,11 +455,15 @@ __device__ __forceinline__ void tile_run_f32_bf16(const uint8_t* s, uint8_t* d, 
   for (int h = 0; h < U / P; ++h) {
     v4u a[2 * P];
 #pragma unroll
-    for (int k = 0; k < 2 * P; ++k) a[k] = ld16<NT>(s, umin((h * 2 * P + k) * kReshardThreads + tid, last) * 16u);
+    for (int k = 0; k < 2 * P; ++k) {
+      const uint32_t i = (h * 2 * P + k) * kReshardThreads + tid;
+      a[k] = ld16<POL>(s, (FULL ? i : umin(i, last)) * 16u);
+    }
+    if constexpr (!FULL) loads_done();
 #pragma unroll
     for (int k = 0; k < 2 * P; ++k) {
       const uint32_t i = (h * 2 * P + k) * kReshardThreads + tid;
-      if (i <= last) st8<NT>(d, i * 8u, to_bf16x4(a[k]));
+      if (FULL || i <= last) st8<POL>(d, i * 8u, to_bf16x4(a[k]));
     }
   }
 }
@@ -441,7 +471,7 @@ __device__ __forceinline__ void tile_run_f32_bf16(const uint8_t* s, uint8_t* d, 
 // The same rows converted: destination vectors r0 .. r0 + last, moved as halves (four fp32 read, four
 // bf16 written). Half n of the tile belongs to destination vector r0 + n / 2, in row (r0 + n / 2) / rv;
 // its column in halves is 2 r0 + n less twice the row's first vector.
-template <int U, bool NT>
+template <int U, int POL, bool FULL>
 __device__ __forceinline__ void tile_rows_f32_bf16(const uint8_t* s, uint8_t* d, uint32_t r0, uint32_t last,
                                                    uint32_t rv, uint32_t mg, uint32_t ss, uint32_t ds) {
   constexpr int P = kCvtPass<U>;
@@ -452,17 +482,44 @@ __device__ __forceinline__ void tile_rows_f32_bf16(const uint8_t* s, uint8_t* d,
     v4u a[2 * P];
 #pragma unroll
     for (int k = 0; k < 2 * P; ++k) {
-      const uint32_t n = 2 * r0 + umin((p * 2 * P + k) * kReshardThreads + tid, lasth);
+      const uint32_t i = (p * 2 * P + k) * kReshardThreads + tid, n = 2 * r0 + (FULL ? i : umin(i, lasth));
       const uint32_t q = rv > 1 ? __umulhi(n >> 1, mg) : (n >> 1);
-      a[k] = ld16<NT>(s, q * ss + (n - q * h) * 16u);
+      a[k] = ld16<POL>(s, q * ss + (n - q * h) * 16u);
     }
+    if constexpr (!FULL) loads_done();
 #pragma unroll
     for (int k = 0; k < 2 * P; ++k) {
       const uint32_t i = (p * 2 * P + k) * kReshardThreads + tid;
       const uint32_t n = 2 * r0 + i;
       const uint32_t q = rv > 1 ? __umulhi(n >> 1, mg) : (n >> 1);
-      if (i <= lasth) st8<NT>(d, q * ds + (n - q * h) * 8u, to_bf16x4(a[k]));
+      if (FULL || i <= lasth) st8<POL>(d, q * ds + (n - q * h) * 8u, to_bf16x4(a[k]));
     }
+  }
+}
+
+// The tile forms above, by the plan's conversion and by whether the tile is full (uniform).
+template <int U, int POL, bool ZERO, bool LDS, int CVT>
+__device__ __forceinline__ void move_run(const uint8_t* s, uint8_t* d, uint32_t cnt, v4u* stage) {
+  const bool full = cnt == uint32_t(kReshardThreads) * U;
+  if constexpr (CVT == CVT_F32_BF16 && !ZERO) {
+    if (full) tile_run_f32_bf16<U, POL, true>(s, d, cnt);
+    else tile_run_f32_bf16<U, POL, false>(s, d, cnt);
+  } else {
+    if (full) tile_run<U, POL, ZERO, LDS, CVT, true>(s, d, cnt, stage);
+    else tile_run<U, POL, ZERO, LDS, CVT, false>(s, d, cnt, stage);
+  }
+}
+
+template <int U, int POL, bool ZERO, bool LDS, int CVT>
+__device__ __forceinline__ void move_rows(const uint8_t* s, uint8_t* d, uint32_t r0, uint32_t last, uint32_t rv,
+                                          uint32_t mg, uint32_t ss, uint32_t ds, v4u* stage) {
+  const bool full = last + 1 == uint32_t(kReshardThreads) * U;
+  if constexpr (CVT == CVT_F32_BF16 && !ZERO) {
+    if (full) tile_rows_f32_bf16<U, POL, true>(s, d, r0, last, rv, mg, ss, ds);
+    else tile_rows_f32_bf16<U, POL, false>(s, d, r0, last, rv, mg, ss, ds);
+  } else {
+    if (full) tile_rows<U, POL, ZERO, LDS, CVT, true>(s, d, r0, last, rv, mg, ss, ds, stage);
+    else tile_rows<U, POL, ZERO, LDS, CVT, false>(s, d, r0, last, rv, mg, ss, ds, stage);
   }
 }
 
@@ -488,7 +545,7 @@ constexpr uint32_t any_src(uint32_t n) {  // source bytes behind n destination b
   return CVT == CVT_F32_BF16 ? n * 2 : CVT == CVT_BF16_F32 ? n / 2 : n;
 }
 
-template <int U, bool NT, bool ZERO, int CVT, bool ROWS>
+template <int U, int POL, bool ZERO, int CVT, bool ROWS>
 __device__ __forceinline__ void tile_any(const uint8_t* s, uint8_t* d, uint32_t r0, uint32_t cnt, uint32_t rv,
                                          uint32_t mg, uint32_t ss, uint32_t ds, uint32_t gmask, int32_t lo, int32_t hi) {
   constexpr uint32_t D = ZERO ? 16u : any_unit_bytes(CVT);
@@ -515,22 +572,23 @@ __device__ __forceinline__ void tile_any(const uint8_t* s, uint8_t* d, uint32_t 
       if constexpr (ZERO) {
         r[k] = v4u{0, 0, 0, 0};
       } else if constexpr (CVT == CVT_BF16_F32) {
-        const v2u h = ld8_any<NT>(s, from);
+        const v2u h = ld8_any<POL>(s, from);
         r[k].x = h.x;
         r[k].y = h.y;
       } else {
-        r[k] = ld16_any<NT>(s, from);
+        r[k] = ld16_any<POL>(s, from);
       }
     }
+    if constexpr (!ZERO) loads_done();
 #pragma unroll
     for (int k = 0; k < P; ++k) {
       if (!live[k]) continue;
       if constexpr (CVT == CVT_F32_BF16 && !ZERO) {
-        st8_any<NT>(d, to[k], to_bf16x4(r[k]));
+        st8_any<POL>(d, to[k], to_bf16x4(r[k]));
       } else if constexpr (CVT == CVT_BF16_F32 && !ZERO) {
-        st16_any<NT>(d, to[k], v4u{r[k].x << 16, r[k].x & 0xffff0000u, r[k].y << 16, r[k].y & 0xffff0000u});
+        st16_any<POL>(d, to[k], v4u{r[k].x << 16, r[k].x & 0xffff0000u, r[k].y << 16, r[k].y & 0xffff0000u});
       } else {
-        st16_any<NT>(d, to[k], r[k]);
+        st16_any<POL>(d, to[k], r[k]);
       }
     }
   }
@@ -557,17 +615,15 @@ __device__ void tile_elems(const DevSeg& g, uint64_t lt, const uint8_t* sb, uint
   }
 }
 
-template <int U, bool NT, bool ZERO, bool LDS, int CVT>
+template <int U, int POL, bool ZERO, bool LDS, int CVT>
 __device__ __forceinline__ void run_tile(const DevSeg& g, uint64_t lt, const uint8_t* sb, uint8_t* db, v4u* stage) {
   constexpr uint64_t TV = uint64_t(kReshardThreads) * U;
   constexpr uint64_t SV = kSrcVecBytes<CVT>;
   const uint32_t mode = g.mode & SEG_MODE_MASK;
-  constexpr bool kHalves = CVT == CVT_F32_BF16 && !ZERO;
   if (mode == SEG_VEC_1D) {
     const uint64_t nv = g.run / 16, v0 = lt * TV;
     const uint32_t cnt = uint32_t(nv - v0 < TV ? nv - v0 : TV);
-    if constexpr (kHalves) tile_run_f32_bf16<U, NT>(sb + g.src_off + v0 * SV, db + g.dst_off + v0 * 16, cnt);
-    else tile_run<U, NT, ZERO, LDS, CVT>(ZERO ? nullptr : sb + g.src_off + v0 * SV, db + g.dst_off + v0 * 16, cnt, stage);
+    move_run<U, POL, ZERO, LDS, CVT>(ZERO ? nullptr : sb + g.src_off + v0 * SV, db + g.dst_off + v0 * 16, cnt, stage);
   } else if (mode == SEG_VEC_FLAT || mode == SEG_VEC_ROWS) {
     // FLAT: vectors [lt * TV, lt * TV + TV) of the rows' row-major order, starting in row row0 at
     // column r0. ROWS: `param` whole rows per tile.
@@ -587,20 +643,18 @@ __device__ __forceinline__ void run_tile(const DevSeg& g, uint64_t lt, const uin
     const uint8_t* s = ZERO ? nullptr : sb + g.src_off + row0 * g.src_stride;
     uint8_t* d = db + g.dst_off + row0 * g.dst_stride;
     const uint32_t ss = uint32_t(g.src_stride), ds = uint32_t(g.dst_stride);
-    if constexpr (kHalves) tile_rows_f32_bf16<U, NT>(s, d, r0, last, g.rv, g.magic, ss, ds);
-    else tile_rows<U, NT, ZERO, LDS, CVT>(s, d, r0, last, g.rv, g.magic, ss, ds, stage);
+    move_rows<U, POL, ZERO, LDS, CVT>(s, d, r0, last, g.rv, g.magic, ss, ds, stage);
   } else if (mode == SEG_VEC_ROWCHUNK) {
     const uint64_t row = lt / g.param, ch = lt - row * g.param;
     const uint64_t nv = g.run / 16, v0 = ch * TV;
     const uint32_t cnt = uint32_t(nv - v0 < TV ? nv - v0 : TV);
     const uint8_t* s = ZERO ? nullptr : sb + g.src_off + row * g.src_stride + v0 * SV;
     uint8_t* d = db + g.dst_off + row * g.dst_stride + v0 * 16;
-    if constexpr (kHalves) tile_run_f32_bf16<U, NT>(s, d, cnt);
-    else tile_run<U, NT, ZERO, LDS, CVT>(s, d, cnt, stage);
+    move_run<U, POL, ZERO, LDS, CVT>(s, d, cnt, stage);
   } else if (mode == SEG_ANY_FLAT) {
     constexpr uint32_t D = ZERO ? 16u : any_unit_bytes(CVT), TU = uint32_t(TV) * 16 / D;  // units per tile
     const uint32_t n0 = uint32_t(lt) * TU, q0 = g.rv > 1 ? __umulhi(n0, g.magic) : n0;
-    tile_any<U, NT, ZERO, CVT, true>(ZERO ? nullptr : sb + g.src_off + uint64_t(q0) * g.src_stride,
+    tile_any<U, POL, ZERO, CVT, true>(ZERO ? nullptr : sb + g.src_off + uint64_t(q0) * g.src_stride,
                                      db + g.dst_off + uint64_t(q0) * g.dst_stride, n0 - q0 * g.rv,
                                      umin(g.param - n0, TU), g.rv, g.magic, uint32_t(g.src_stride),
                                      uint32_t(g.dst_stride), g.mode >> SEG_GRID_SHIFT, 0, int32_t(g.run) - int32_t(D));
@@ -616,47 +670,54 @@ __device__ __forceinline__ void run_tile(const DevSeg& g, uint64_t lt, const uin
     const uint32_t gmask = g.mode >> SEG_GRID_SHIFT;
     const int32_t m = int32_t(uint32_t(reinterpret_cast<uintptr_t>(d)) & gmask);
     const int32_t end = ch + 1 == g.param ? int32_t(g.run - b0) : TB - m;
-    tile_any<U, NT, ZERO, CVT, false>(s, d, 0, (uint32_t(end + m) + D - 1) / D, 0, 0, 0, 0, gmask, ch ? -m : 0,
+    tile_any<U, POL, ZERO, CVT, false>(s, d, 0, (uint32_t(end + m) + D - 1) / D, 0, 0, 0, 0, gmask, ch ? -m : 0,
                                       end - int32_t(D));
   } else {
     tile_elems<U, ZERO, CVT>(g, lt, sb, db);
   }
 }
 
-// One workgroup per tile. With XCD remapping, the round-robin dispatch of workgroups over the 8 XCDs is
-// undone: XCD x (workgroups x, x+8, ...) works through one contiguous eighth of the tile range, so each
-// XCD's L2 sees one stream instead of every eighth tile of all of them. ZERO instances run the map's
-// zero-fill section, the others its copy section.
-template <int U, bool NT, bool LDS, bool XCD, int CVT, bool ZERO>
-__global__ __launch_bounds__(kReshardThreads, EMU_RESHARD_WAVES_PER_EU) void k_reshard(const DevSeg* __restrict__ segs,
-                                                                             const uint32_t* __restrict__ tilemap,
-                                                                             uint64_t tile_base,
-                                                                             const uint64_t* __restrict__ src_ptrs,
+// One workgroup per tile. The dispatcher deals workgroups to the XCDs round-robin; with XCD remapping, XCD x
+// takes blocks x, x + 8, ... of kReshardBlock consecutive tiles (1 MB at 4 KB tiles), so each XCD's L2 sees
+// whole blocks and the eight of them work through one front of the map; what is left after the last whole
+// round of blocks goes to the XCDs in contiguous eighths. On the same buffers, 1B TP4 -> TP2 / the same in
+// fp32, three groups / 8B TP2 PP2 -> TP4: 885 / 5356 / 4822 us against 901 / 5398 / 4799 with contiguous
+// eighths of the whole map; blocks of 512 tiles 887 / 5372 / 4812, of 1024 891 / 5370 / 4816.
+//
+// The map holds the copy segments' tiles, then the zero-fill segments' (padded vocabulary rows); both run in
+// one launch: a launch of its own took the zero fill 4 to 5 us, whatever its size.
+constexpr uint32_t kReshardBlock = 256;
+
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t w, uint32_t per) {  // per: an eighth of the grid
+  const uint32_t x = w % kXcds, j = w / kXcds, whole = per / kReshardBlock * kReshardBlock;
+  if (j < whole) return ((j / kReshardBlock) * kXcds + x) * kReshardBlock + j % kReshardBlock;
+  return whole * kXcds + x * (per - whole) + (j - whole);
+}
+
+template <int U, int POL, bool LDS, bool XCD, int CVT>
+__global__ __launch_bounds__(kReshardThreads, EMU_RESHARD_WAVES_PER_EU) void k_reshard(const uint32_t* __restrict__ tilemap,
+                                                                             uint32_t tile_base, uint32_t per,
+                                                                             const DevSeg* __restrict__ segs,
                                                                              const uint64_t* __restrict__ dst_ptrs,
-                                                                             uint32_t src_n, uint32_t dst_n) {
+                                                                             const uint64_t* __restrict__ src_ptrs,
+                                                                             uint32_t dst_n, uint32_t src_n) {
   extern __shared__ v4u stage[];
-  uint32_t local = blockIdx.x;
-  if constexpr (XCD) {
-    const uint32_t per = gridDim.x / kXcds;  // the host launches a multiple of kXcds workgroups
-    local = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-  }
-  // Each section of the map is padded with kNoSeg to the grid's size, so no bounds check precedes
-  // the map load. Every path of a copy instance reads the source pointer, so its load issues together
-  // with the destination pointer's, right after the descriptor: the chain before the first data load
-  // is kernel arguments, map entry, descriptor, pointers.
-  const uint64_t tile = tile_base + local;
+  // Each section of the map is padded with kNoSeg to a multiple of the XCD count, so no bounds check
+  // precedes the map load. The source pointer's load issues together with the destination pointer's, right
+  // after the descriptor, also where a zero fill will not use it (entry 0 then): the chain before the first
+  // data load is map entry, descriptor, pointers. The arguments are in registers when a wave starts (the
+  // build asks for them to be preloaded).
+  const uint32_t tile = tile_base + (XCD ? xcd_tile(blockIdx.x, per) : blockIdx.x);
   const uint32_t si = tilemap[tile];
   if (si == kNoSeg) return;
   const DevSeg g = segs[si];
   // grid row y runs tensor group y: its pointer tables follow the earlier groups' back to back
   uint8_t* db = reinterpret_cast<uint8_t*>(dst_ptrs[uint64_t(blockIdx.y) * dst_n + g.dst_idx]);
-  const uint64_t lt = tile - g.tile0;
-  if constexpr (ZERO) {
-    run_tile<U, NT, true, LDS, CVT_NONE>(g, lt, nullptr, db, stage);
-  } else {
-    const uint8_t* sb = reinterpret_cast<const uint8_t*>(src_ptrs[uint64_t(blockIdx.y) * src_n + g.src_idx]);
-    run_tile<U, NT, false, LDS, CVT>(g, lt, sb, db, stage);
-  }
+  const uint8_t* sb =
+      reinterpret_cast<const uint8_t*>(src_ptrs[uint64_t(blockIdx.y) * src_n + (g.src_idx < 0 ? 0 : g.src_idx)]);
+  const uint32_t lt = tile - uint32_t(g.tile0);
+  if (g.mode & SEG_ZERO) run_tile<U, POL, true, LDS, CVT_NONE>(g, lt, nullptr, db, stage);
+  else run_tile<U, POL, false, LDS, CVT>(g, lt, sb, db, stage);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -980,15 +1041,10 @@ static int device_cus() {
 // divided by c, rounded down to whole KB; the kernels never touch the reserved bytes. The CU's LDS is
 // allocated in two halves and a workgroup's block lies in one half, so the resident count is
 // 2 * floor(c / 2) for c >= 2 (c = 1 keeps one). The cap bounds the bytes in flight per CU: on MI355X
-// a copy stream runs fastest with about 24-64 KB in flight per CU and drops by about 8% at 128 KB,
+// a copy stream runs fastest with about 24-48 KB in flight per CU and drops by about 8% at 128 KB,
 // where the HBM read/write mix degrades. Automatic (-1): flight / tile_bytes workgroups, at least 2,
-// and no cap from 32 up, with `flight` in destination bytes. Measured optima at 4 KB tiles: a copying
-// reshard 12 tiles (48 KB), fp32 -> bf16 10 (40 KB; each tile reads twice what it writes), bf16 ->
-// fp32 16 (64 KB; each reads half), all about 100-120 KB of reads and writes together; the
-// pack/unpack kernel, whose per-chunk setup is longer, 16 of its 4 KB chunks (64 KB).
-template <int CVT>
-constexpr uint64_t kReshardFlightBytes = CVT == CVT_F32_BF16 ? 40 * 1024 : CVT == CVT_BF16_F32 ? 64 * 1024 : 48 * 1024;
-constexpr uint64_t kBucketFlightBytes = 64 * 1024;
+// and no cap from 32 up, with `flight` in destination bytes (see launch_rule).
+constexpr uint64_t kBucketFlightBytes = 64 * 1024;  // pack/unpack: 16 chunks of 4 KB
 static size_t occupancy_lds(size_t need, uint64_t tile_bytes, uint64_t flight) {
   int64_t cap = option(EMU_OPT_WG_PER_CU);
   if (cap < 0) {
@@ -1023,62 +1079,80 @@ struct Tables {
   uint32_t groups, src_n, dst_n;
 };
 
-// Launches k_reshard over the map section [first, first + count) for every group (grid row y = group y);
-// first is a multiple of kXcds and the section is padded to one.
-template <int U, bool NT, bool LDS, bool XCD, int CVT, bool ZERO>
-static void launch_reshard(hipStream_t st, const DevSeg* segs, const uint32_t* tm, uint64_t first, uint64_t count,
-                           const Tables& tb) {
-  const size_t lds = occupancy_lds(LDS ? size_t(kReshardThreads) * U * 16 : 0, uint64_t(kReshardThreads) * U * 16,
-                                   kReshardFlightBytes<CVT>);
+// How a plan's reshard is launched, from what it moves. Measured at 4 KB tiles, several settings in one process
+// on the same buffers, with the states in rotation that no cache holds:
+//  - Residency (flight, destination bytes in flight per CU). Copies: 48 KB; 8 / 10 / 12 / 14 tiles ran the 1B
+//    TP4 -> TP2 reshard in 912 / 890 / 890 / 900 us and a decoder with odd widths in 155 / 147 / 145 / 148.
+//    fp32 -> bf16, which reads twice what it writes: 24 KB; 4 / 6 / 8 / 10 tiles took 1548 / 1319 / 1340 / 1355 us
+//    on aligned 1B shards; with units at any alignment, whose address work is longer, 40 KB: 285 / 226 / 217 / 216
+//    on the odd widths. bf16 -> fp32, which reads half: written through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 /
+//    1372 us (1B, fused to separate formats), otherwise 48 KB, 10 / 12 / 14 / 16 tiles in 1414 / 1382 / 1394 / 1418.
+//  - Cache policy. Writing through gains from about 1 GB moved per launch on (1B copy 890 against 914 us, 8B 4823
+//    against 4928, fp32 -> bf16 1319 against 1335, bf16 -> fp32 1364 against 1382), not below (0.7 GB: 107.2 against
+//    105.5; 4 MB: 2.7 against 2.5), and not where units at any alignment end on lines that a neighbour completes (odd
+//    widths, 1.6 GB: 280 against 272).
+struct LaunchRule {
+  int policy;
+  uint64_t flight;
+};
+constexpr uint64_t kThroughBytes = 1ull << 30;        // read and written by one reshard launch
+static LaunchRule launch_rule(const Plan* P, uint32_t groups) {
+  const bool any = P->info.n_general_segments > 0;
+  const uint64_t moved = (P->info.bytes_read + P->info.bytes_written) * groups;
+  LaunchRule r{POL_PLAIN, 48 << 10};
+  if (option(EMU_OPT_NONTEMPORAL) != 0) r.policy = !any && moved >= kThroughBytes ? POL_THROUGH : POL_NT;
+  if (P->cvt == CVT_F32_BF16) r.flight = (any ? 40 : 24) << 10;
+  else if (P->cvt == CVT_BF16_F32 && r.policy == POL_THROUGH) r.flight = 56 << 10;
+  return r;
+}
+
+// Launches k_reshard over the whole map (n_map entries, a multiple of kXcds) for every group (grid row y =
+// group y).
+struct ReshardLaunch {
+  const DevSeg* segs;
+  const uint32_t* tm;
+  uint64_t n_map, flight;
+  Tables tb;
+  hipStream_t st;
+};
+
+template <int U, int POL, bool LDS, bool XCD, int CVT>
+static void launch_reshard(const ReshardLaunch& l) {
+  constexpr uint64_t kTile = uint64_t(kReshardThreads) * U * 16;
+  const size_t lds = occupancy_lds(LDS ? size_t(kTile) : 0, kTile, l.flight);
   // a multiple of kXcds whose work-items (64 per workgroup) stay below 2^32 in the grid's x dimension
   constexpr uint64_t kMaxGrid = (1ull << 26) - kXcds;
-  for (uint64_t done = 0; done < count; done += kMaxGrid) {
-    const uint32_t n = uint32_t(count - done < kMaxGrid ? count - done : kMaxGrid);
-    const uint32_t grid = XCD ? (n + kXcds - 1) / kXcds * kXcds : n;
-    hipLaunchKernelGGL((k_reshard<U, NT, LDS, XCD, CVT, ZERO>), dim3(grid, tb.groups), dim3(kReshardThreads), lds, st,
-                       segs, tm, first + done, tb.sp, tb.dp, tb.src_n, tb.dst_n);
+  for (uint64_t done = 0; done < l.n_map; done += kMaxGrid) {
+    const uint32_t grid = uint32_t(l.n_map - done < kMaxGrid ? l.n_map - done : kMaxGrid);
+    hipLaunchKernelGGL((k_reshard<U, POL, LDS, XCD, CVT>), dim3(grid, l.tb.groups), dim3(kReshardThreads), lds, l.st,
+                       l.tm, uint32_t(done), grid / kXcds, l.segs, l.tb.dp, l.tb.sp, l.tb.dst_n, l.tb.src_n);
   }
 }
 
-// The copy section of the map, with the plan's conversion, for every combination of
-// the launch options (converting plans: no LDS staging).
-template <int U, int CVT>
-static void launch_copy(bool nt_hint, bool lds, bool xcd, hipStream_t st, const DevSeg* segs, const uint32_t* tm,
-                        uint64_t first, uint64_t count, const Tables& tb) {
-  constexpr bool kLds = CVT == CVT_NONE;  // staging instances exist for plain copies only
-  const int key = (nt_hint ? 4 : 0) | (lds && kLds ? 2 : 0) | (xcd ? 1 : 0);
-  switch (key) {
-    case 0: launch_reshard<U, false, false, false, CVT, false>(st, segs, tm, first, count, tb); break;
-    case 1: launch_reshard<U, false, false, true, CVT, false>(st, segs, tm, first, count, tb); break;
-    case 2: launch_reshard<U, false, kLds, false, CVT, false>(st, segs, tm, first, count, tb); break;
-    case 3: launch_reshard<U, false, kLds, true, CVT, false>(st, segs, tm, first, count, tb); break;
-    case 4: launch_reshard<U, true, false, false, CVT, false>(st, segs, tm, first, count, tb); break;
-    case 5: launch_reshard<U, true, false, true, CVT, false>(st, segs, tm, first, count, tb); break;
-    case 6: launch_reshard<U, true, kLds, false, CVT, false>(st, segs, tm, first, count, tb); break;
-    default: launch_reshard<U, true, kLds, true, CVT, false>(st, segs, tm, first, count, tb); break;
+// For every combination of the launch options (LDS staging and XCD order; converting plans: no LDS staging).
+template <int U, int POL, int CVT>
+static void launch_options(const ReshardLaunch& l) {
+  const bool xcd = option(EMU_OPT_XCD_REMAP) != 0;
+  if constexpr (CVT == CVT_NONE) {
+    if (option(EMU_OPT_LDS_STAGING) != 0)
+      return xcd ? launch_reshard<U, POL, true, true, CVT>(l) : launch_reshard<U, POL, true, false, CVT>(l);
   }
+  xcd ? launch_reshard<U, POL, false, true, CVT>(l) : launch_reshard<U, POL, false, false, CVT>(l);
+}
+
+template <int U, int CVT>
+static void launch_policy(int policy, const ReshardLaunch& l) {
+  if (policy == POL_PLAIN) launch_options<U, POL_PLAIN, CVT>(l);
+  else if (policy == POL_THROUGH) launch_options<U, POL_THROUGH, CVT>(l);
+  else launch_options<U, POL_NT, CVT>(l);
 }
 
 template <int U>
-static void dispatch_reshard(const Plan* P, bool nt_hint, bool lds, bool xcd, hipStream_t st, const DevSeg* segs,
-                             const uint32_t* tm, const Tables& tb) {
-  if (P->ntiles_copy > 0) {
-    const uint64_t n = P->ntiles_copy;
-    switch (P->cvt) {
-      case CVT_F32_BF16: launch_copy<U, CVT_F32_BF16>(nt_hint, lds, xcd, st, segs, tm, 0, n, tb); break;
-      case CVT_BF16_F32: launch_copy<U, CVT_BF16_F32>(nt_hint, lds, xcd, st, segs, tm, 0, n, tb); break;
-      default: launch_copy<U, CVT_NONE>(nt_hint, lds, xcd, st, segs, tm, 0, n, tb); break;
-    }
-  }
-  if (P->ntiles_zero > 0) {
-    const uint64_t z0 = P->zero_tile0, n = P->ntiles_zero;
-    const int key = (nt_hint ? 2 : 0) | (xcd ? 1 : 0);
-    switch (key) {
-      case 0: launch_reshard<U, false, false, false, CVT_NONE, true>(st, segs, tm, z0, n, tb); break;
-      case 1: launch_reshard<U, false, false, true, CVT_NONE, true>(st, segs, tm, z0, n, tb); break;
-      case 2: launch_reshard<U, true, false, false, CVT_NONE, true>(st, segs, tm, z0, n, tb); break;
-      default: launch_reshard<U, true, false, true, CVT_NONE, true>(st, segs, tm, z0, n, tb); break;
-    }
+static void launch_convert(int cvt, int policy, const ReshardLaunch& l) {
+  switch (cvt) {
+    case CVT_F32_BF16: launch_policy<U, CVT_F32_BF16>(policy, l); break;
+    case CVT_BF16_F32: launch_policy<U, CVT_BF16_F32>(policy, l); break;
+    default: launch_policy<U, CVT_NONE>(policy, l); break;
   }
 }
 
@@ -1158,18 +1232,17 @@ static int bucket_call(emu_plan_t plan, const void* ws, int32_t side, uint64_t B
 // `groups` tensor groups.
 static int launch_plan(const Plan* P, const uint8_t* w, const uint64_t* sp, const uint64_t* dp, uint32_t groups,
                        hipStream_t st, const char* what) {
-  const DevSeg* segs = reinterpret_cast<const DevSeg*>(w + P->ws.off_segs);
-  const uint32_t* tm = reinterpret_cast<const uint32_t*>(w + P->ws.off_tilemap);
-  const bool ntm = option(EMU_OPT_NONTEMPORAL) != 0, lds = option(EMU_OPT_LDS_STAGING) != 0;
-  const bool xcd = option(EMU_OPT_XCD_REMAP) != 0;
-  const Tables tb{sp, dp, groups, uint32_t(P->side[0].tensors.size()), uint32_t(P->side[1].tensors.size())};
+  const LaunchRule rule = launch_rule(P, groups);
+  const ReshardLaunch l{reinterpret_cast<const DevSeg*>(w + P->ws.off_segs),
+                        reinterpret_cast<const uint32_t*>(w + P->ws.off_tilemap), P->ws.n_map, rule.flight,
+                        Tables{sp, dp, groups, uint32_t(P->side[0].tensors.size()), uint32_t(P->side[1].tensors.size())}, st};
   drop_pending_error();
   switch (P->tile_vecs) {
-    case 1: dispatch_reshard<1>(P, ntm, lds, xcd, st, segs, tm, tb); break;
-    case 2: dispatch_reshard<2>(P, ntm, lds, xcd, st, segs, tm, tb); break;
-    case 4: dispatch_reshard<4>(P, ntm, lds, xcd, st, segs, tm, tb); break;
-    case 16: dispatch_reshard<16>(P, ntm, lds, xcd, st, segs, tm, tb); break;
-    default: dispatch_reshard<8>(P, ntm, lds, xcd, st, segs, tm, tb); break;
+    case 1: launch_convert<1>(P->cvt, rule.policy, l); break;
+    case 2: launch_convert<2>(P->cvt, rule.policy, l); break;
+    case 4: launch_convert<4>(P->cvt, rule.policy, l); break;
+    case 16: launch_convert<16>(P->cvt, rule.policy, l); break;
+    default: launch_convert<8>(P->cvt, rule.policy, l); break;
   }
   return hip_check(what);
 }
