@@ -14,6 +14,7 @@
 #include <atomic>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "emu_internal.h"
 
@@ -172,160 +173,40 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 // CU the 1B TP4 -> TP2 reshard took 957 us with both, 1,086 us before; at 8 per CU 926 against 962.
 __device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
 
-// 16 bytes starting `sh` bytes (0 < sh < 16) into the 32-byte pair (lo, hi). Q = sh / 4 is a
-// template parameter so that the dword selection is static; the byte shift uses v_alignbyte.
-template <int Q>
-__device__ __forceinline__ v4u funnel(v4u lo, v4u hi, uint32_t b) {
-  const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-  v4u o;
-  o.x = __builtin_amdgcn_alignbyte(w[Q + 1], w[Q + 0], b);
-  o.y = __builtin_amdgcn_alignbyte(w[Q + 2], w[Q + 1], b);
-  o.z = __builtin_amdgcn_alignbyte(w[Q + 3], w[Q + 2], b);
-  o.w = __builtin_amdgcn_alignbyte(w[Q + 4], w[Q + 3], b);
-  return o;
-}
-
-// Workgroup-cooperative copy of nv 16-byte vectors, both sides 16-byte aligned (ZERO: store zeros).
-// nv * 16 must fit in 32 bits: offsets are 32-bit from uniform base pointers. Lanes past the end load
-// the last valid vector again (so every load is unconditional and all U are in flight together) and
-// skip their store.
-template <int NTH, int U, bool NT, bool ZERO>
-__device__ __forceinline__ void wg_vec_copy(const uint8_t* __restrict__ s, uint8_t* __restrict__ d, uint32_t nv) {
+// Workgroup-cooperative copy of n > 0 bytes between any even addresses (n < 2^31). The body runs in 16-byte
+// units on the destination's 16-byte grid; the first and the last unit are moved inward to the copy's ends
+// and overlap their neighbours, which write the same bytes there. P units per lane are in flight. m is the
+// phase of d on the grid, known from the tables (tensors and buckets are 16-byte aligned), so that the loads
+// need not wait for the destination's pointer.
+template <int NTH, int P, int POL>
+__device__ __forceinline__ void wg_copy(const uint8_t* __restrict__ s, uint8_t* __restrict__ d, uint32_t n, uint32_t m) {
   const uint32_t tid = threadIdx.x;
-  constexpr uint32_t TV = uint32_t(NTH) * U;
+  constexpr uint32_t kFull = uint32_t(NTH) * P * 16u;
+  if (n == kFull && m == 0) {
+    v4u r[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) r[k] = ld16_any<POL>(s, (k * NTH + tid) * 16u);
+#pragma unroll
+    for (int k = 0; k < P; ++k) st16<POL>(d, (k * NTH + tid) * 16u, r[k]);
+  } else if (n >= 16u) {
+    const uint32_t cnt = (n + m + 15u) / 16u;
 #pragma nounroll
-  for (uint32_t base = 0; base < nv; base += TV) {
-    const uint32_t last = umin(nv - base, TV) - 1;
-    v4u r[U];
+    for (uint32_t b = 0; b < cnt; b += uint32_t(NTH) * P) {
+      uint32_t at[P];
+      v4u r[P];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if constexpr (ZERO) r[u] = v4u{0, 0, 0, 0};
-      else r[u] = ld16<NT>(s, (base + umin(u * NTH + tid, last)) * 16u);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t i = u * NTH + tid;
-      if (i <= last) st16<NT>(d, (base + i) * 16u, r[u]);
-    }
-  }
-}
-
-// Workgroup-cooperative copies of nv destination-aligned vectors whose source starts `sh` bytes past the
-// 16-byte aligned address sa (0 < sh < 16): output vector i is cut from aligned source vectors i and
-// i + 1 (funnel). Each lane loads vector i; vector i + 1 comes from the next lane through DPP
-// (wave_shl:1, a VALU operand modifier rather than an LDS permute). The last output's second vector is
-// the granule holding the copy's last source byte, so no read leaves the granules the copy's own bytes
-// occupy.
-//
-// One wave per workgroup: lane 63 of a block of 64 vectors takes lane 0 of the next block through
-// wave_rol:1, and only lane 63 of a pass's last block loads a vector of its own (one masked load per
-// pass). Lanes past the end load vector last + 1, so lane `last` finds its second vector in the next lane.
-template <int U, bool NT, int Q>
-__device__ __forceinline__ void wave_shift_copy(const uint8_t* __restrict__ sa, uint8_t* __restrict__ d, uint32_t nv,
-                                                uint32_t b) {
-  const uint32_t lane = threadIdx.x;
-  constexpr uint32_t TV = 64u * U;
-#pragma nounroll
-  for (uint32_t base = 0; base < nv; base += TV) {
-    const uint32_t last = umin(nv - base, TV) - 1;
-    v4u lo[U + 1];
-#pragma unroll
-    for (int u = 0; u < U; ++u) lo[u] = ld16<NT>(sa, (base + umin(u * 64u + lane, last + 1)) * 16u);
-    lo[U] = v4u{0, 0, 0, 0};
-    if (lane == 63u) lo[U] = ld16<NT>(sa, (base + umin(TV - 1, last) + 1u) * 16u);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t i = u * 64u + lane;
-      v4u nx, hi;
-      if (u + 1 < U) {
-        nx.x = __builtin_amdgcn_update_dpp(0u, lo[u + 1].x, 0x134, 0xf, 0xf, false);  // wave_rol:1
-        nx.y = __builtin_amdgcn_update_dpp(0u, lo[u + 1].y, 0x134, 0xf, 0xf, false);
-        nx.z = __builtin_amdgcn_update_dpp(0u, lo[u + 1].z, 0x134, 0xf, 0xf, false);
-        nx.w = __builtin_amdgcn_update_dpp(0u, lo[u + 1].w, 0x134, 0xf, 0xf, false);
-      } else {
-        nx = lo[U];
+      for (int k = 0; k < P; ++k) {
+        const uint32_t x = umin(b + k * NTH + tid, cnt - 1) * 16u;
+        at[k] = umin(x < m ? 0u : x - m, n - 16u);
+        r[k] = ld16_any<POL>(s, at[k]);
       }
-      // wave_shl:1; lane 63 has no source lane and keeps nx
-      hi.x = __builtin_amdgcn_update_dpp(nx.x, lo[u].x, 0x130, 0xf, 0xf, false);
-      hi.y = __builtin_amdgcn_update_dpp(nx.y, lo[u].y, 0x130, 0xf, 0xf, false);
-      hi.z = __builtin_amdgcn_update_dpp(nx.z, lo[u].z, 0x130, 0xf, 0xf, false);
-      hi.w = __builtin_amdgcn_update_dpp(nx.w, lo[u].w, 0x130, 0xf, 0xf, false);
-      if (i <= last) st16<NT>(d, (base + i) * 16u, funnel<Q>(lo[u], hi, b));
-    }
-  }
-}
-
-// Several waves per workgroup: lane 63 of every wave, and the lanes from the last output on, load their
-// second vector themselves.
-template <int NTH, int U, bool NT, int Q>
-__device__ __forceinline__ void wg_shift_copy(const uint8_t* __restrict__ sa, uint8_t* __restrict__ d, uint32_t nv,
-                                              uint32_t b) {
-  const uint32_t tid = threadIdx.x, lane = tid & 63u;
-  constexpr uint32_t TV = uint32_t(NTH) * U;
-#pragma nounroll
-  for (uint32_t base = 0; base < nv; base += TV) {
-    const uint32_t last = umin(nv - base, TV) - 1;
-    v4u lo[U], own[U];
+      loads_done();
 #pragma unroll
-    for (int u = 0; u < U; ++u) lo[u] = ld16<NT>(sa, (base + umin(u * NTH + tid, last)) * 16u);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {  // issued before any wait, next to the loads above
-      const uint32_t i = u * NTH + tid;
-      own[u] = v4u{0, 0, 0, 0};
-      if (lane == 63u || i >= last) own[u] = ld16<NT>(sa, (base + umin(i, last) + 1u) * 16u);
+      for (int k = 0; k < P; ++k)
+        if (b + k * NTH + tid < cnt) st16_any<POL>(d, at[k], r[k]);
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t i = u * NTH + tid;
-      v4u hi;
-      hi.x = __builtin_amdgcn_update_dpp(0u, lo[u].x, 0x130, 0xf, 0xf, false);  // wave_shl:1
-      hi.y = __builtin_amdgcn_update_dpp(0u, lo[u].y, 0x130, 0xf, 0xf, false);
-      hi.z = __builtin_amdgcn_update_dpp(0u, lo[u].z, 0x130, 0xf, 0xf, false);
-      hi.w = __builtin_amdgcn_update_dpp(0u, lo[u].w, 0x130, 0xf, 0xf, false);
-      if (lane == 63u || i >= last) hi = own[u];
-      if (i <= last) st16<NT>(d, (base + i) * 16u, funnel<Q>(lo[u], hi, b));
-    }
-  }
-}
-
-// Workgroup-cooperative copy of n bytes (n < 2^32) at any alignment (ZERO: write n zero bytes).
-// The destination drives the split: a head up to the first 16-byte boundary, a vector body and a
-// tail, the head and tail moved byte by byte. UA is the unroll of the co-aligned body, US that of the
-// realigned body (which holds two source vectors per output vector).
-template <int NTH, int UA, int US, bool NT, bool ZERO>
-__device__ __forceinline__ void wg_copy_bytes(const uint8_t* s, uint8_t* d, uint32_t n) {
-  const uint32_t tid = threadIdx.x;
-  const uint32_t head0 = (16u - uint32_t(reinterpret_cast<uintptr_t>(d) & 15)) & 15u;
-  const uint32_t head = head0 < n ? head0 : n;
-  const uint32_t nv = (n - head) / 16u;
-  const uint32_t tail = n - head - nv * 16u;
-  if (tid < head) d[tid] = ZERO ? 0 : s[tid];
-  if (tid < tail) d[head + nv * 16u + tid] = ZERO ? 0 : s[head + nv * 16u + tid];
-  if (nv == 0) return;
-  if constexpr (ZERO) {
-    wg_vec_copy<NTH, UA, NT, true>(nullptr, d + head, nv);
-  } else {
-    const uint32_t sh = uint32_t(reinterpret_cast<uintptr_t>(s + head) & 15);
-    if (sh == 0) {
-      wg_vec_copy<NTH, UA, NT, false>(s + head, d + head, nv);
-    } else {
-      const uint8_t* sa = s + head - sh;
-      if constexpr (NTH == 64) {
-        switch (sh >> 2) {
-          case 0: wave_shift_copy<US, NT, 0>(sa, d + head, nv, sh & 3); break;
-          case 1: wave_shift_copy<US, NT, 1>(sa, d + head, nv, sh & 3); break;
-          case 2: wave_shift_copy<US, NT, 2>(sa, d + head, nv, sh & 3); break;
-          default: wave_shift_copy<US, NT, 3>(sa, d + head, nv, sh & 3); break;
-        }
-      } else {
-        switch (sh >> 2) {
-          case 0: wg_shift_copy<NTH, US, NT, 0>(sa, d + head, nv, sh & 3); break;
-          case 1: wg_shift_copy<NTH, US, NT, 1>(sa, d + head, nv, sh & 3); break;
-          case 2: wg_shift_copy<NTH, US, NT, 2>(sa, d + head, nv, sh & 3); break;
-          default: wg_shift_copy<NTH, US, NT, 3>(sa, d + head, nv, sh & 3); break;
-        }
-      }
-    }
+  } else if (tid < n / 2u) {
+    reinterpret_cast<uint16_t*>(d)[tid] = reinterpret_cast<const uint16_t*>(s)[tid];
   }
 }
 
@@ -342,9 +223,6 @@ __device__ __forceinline__ void wg_copy_bytes(const uint8_t* s, uint8_t* d, uint
 #ifndef EMU_BUCKET_UNROLL
 #define EMU_BUCKET_UNROLL 8
 #endif
-#ifndef EMU_SHIFT_UNROLL
-#define EMU_SHIFT_UNROLL 4
-#endif
 #ifndef EMU_BUCKET_TILE_VECS
 #define EMU_BUCKET_TILE_VECS 4
 #endif
@@ -353,7 +231,6 @@ __device__ __forceinline__ void wg_copy_bytes(const uint8_t* s, uint8_t* d, uint
 #endif
 constexpr int kXcds = int(kXcdCount);  // workgroups are dealt to the XCDs round-robin
 constexpr int kBucketUnroll = EMU_BUCKET_UNROLL;
-constexpr int kShiftUnroll = EMU_SHIFT_UNROLL;
 constexpr int kBucketTileVecs = EMU_BUCKET_TILE_VECS;  // vectors per thread per pass of k_buckets_tile
 constexpr int kBucketTileThreads = EMU_BUCKET_TILE_THREADS;  // workgroup size of k_buckets_tile
 
@@ -744,7 +621,7 @@ __device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
   return v;
 }
 
-template <bool UNPACK, bool NT, int U>
+template <bool UNPACK, int POL, int U>
 __global__ __launch_bounds__(kThreads, EMU_BUCKET_WAVES_PER_EU) void k_buckets(const uint64_t* __restrict__ sizes,
                                                       const uint32_t* __restrict__ rank_first,
                                                       const uint64_t* __restrict__ rank_bytes,
@@ -818,8 +695,8 @@ __global__ __launch_bounds__(kThreads, EMU_BUCKET_WAVES_PER_EU) void k_buckets(c
       uint8_t* tp = reinterpret_cast<uint8_t*>(tensor_ptrs[t0 + ti]) + (pos - toff);
       uint8_t* bp = reinterpret_cast<uint8_t*>(bucket_ptrs[bucket0 + k]) + (pos - k * B);
       const uint32_t n = uint32_t(pend - pos);
-      if constexpr (UNPACK) wg_copy_bytes<kThreads, U, kShiftUnroll, NT, false>(bp, tp, n);
-      else wg_copy_bytes<kThreads, U, kShiftUnroll, NT, false>(tp, bp, n);
+      if constexpr (UNPACK) wg_copy<kThreads, U, POL>(bp, tp, n, uint32_t(pos - toff) & 15u);
+      else wg_copy<kThreads, U, POL>(tp, bp, n, uint32_t(pos - k * B) & 15u);
       pos = pend;
       if (pos == kend) {
         ++k;
@@ -831,20 +708,20 @@ __global__ __launch_bounds__(kThreads, EMU_BUCKET_WAVES_PER_EU) void k_buckets(c
 
 // Tile-per-workgroup variant: one workgroup per 4 KB chunk (kTileChunkBytes) of one rank's stream, in
 // block-cyclic XCD order. The upload-time map gives the chunk's rank and the global index of the tensor
-// holding its first byte, so the tensor's stream offset and pointer load in parallel with the rank's
+// holding its first byte, so the tensor's stream range and pointer load in parallel with the rank's
 // record; the map is padded to the grid, so no bounds check precedes it. The rank's first bucket, the
 // sum over earlier ranks of ceil(bytes / B), comes from the host in a kernel argument for the first
 // kArgRanks ranks, else from a wave64 reduction. The chunk is then cut at tensor and bucket boundaries.
 //
 // Chunk ends sit on the destination's 4 KB grid. For aligned buckets and tensors that is the stream's
-// grid. When it is not (pack into buckets whose size is not a multiple of 4 KB, unpack into tensors whose
-// stream offsets are not), both ends of every chunk move down to the destination's grid, by the same
+// grid. When it is not (REALIGN: pack into buckets whose size is not a multiple of 4 KB, unpack into tensors
+// whose stream offsets are not), both ends of every chunk move down to the destination's grid, by the same
 // rule on either side of each cut, so consecutive chunks still tile the stream. Every destination cache
 // line is then written by one workgroup; cut on the stream's grid, every chunk end would split a line
 // between two workgroups, which costs partial-line writes to HBM.
 constexpr int kArgRanks = 128;
-// Chunks per block of the bucket kernel's XCD order (64 x 4 KB = 256 KB). Contiguous eighths per XCD, the
-// reshard's order, put the eight XCD streams exactly one eighth of the streams apart; on a rank set laid out
+// Chunks per block of the bucket kernel's XCD order (64 x 4 KB = 256 KB). Contiguous eighths per XCD put the
+// eight XCD streams exactly one eighth of the streams apart; on a rank set laid out
 // in one allocation that ran pack and unpack at 75-80% of HBM peak against 82% in per-rank buffers. Blocks of
 // 256 KB ran both layouts at 82%; 64 KB and 128 KB blocks lost 5-12 points, 512 KB to 2 MB blocks 0.3-1.
 constexpr uint32_t kBucketBlock = 64;
@@ -852,69 +729,89 @@ struct BucketBases {
   uint64_t first[kArgRanks];  // first bucket of each rank, for ranks below kArgRanks
 };
 
-template <bool UNPACK, bool NT, int U>
+// floor(x / B) with recip = floor((2^64 - 1) / B): the product's high half is at most two short.
+__device__ __forceinline__ uint64_t div_by(uint64_t x, uint64_t B, uint64_t recip) {
+  uint64_t k = __umul64hi(x, recip);
+  while (x - k * B >= B) ++k;
+  return k;
+}
+
+template <bool UNPACK, int POL, int U, bool REALIGN>
 __global__ __launch_bounds__(kBucketTileThreads, EMU_RESHARD_WAVES_PER_EU) void k_buckets_tile(
-    const uint64_t* __restrict__ stream_off, const uint64_t* __restrict__ rank_info,
-    const uint64_t* __restrict__ rank_bytes, const uint32_t* __restrict__ tile_map, uint64_t B, int32_t b_shift,
-    uint32_t realign, const uint64_t* __restrict__ tensor_ptrs, const uint64_t* __restrict__ bucket_ptrs,
+    const uint32_t* __restrict__ tile_map, uint32_t n_map, const uint64_t* __restrict__ rank_info,
+    const uint64_t* __restrict__ stream_off, const uint64_t* __restrict__ tensor_ptrs,
+    const uint64_t* __restrict__ bucket_ptrs, uint64_t B, uint64_t recip, const uint64_t* __restrict__ rank_bytes,
     BucketBases bases) {
   // Block-cyclic order: the dispatcher deals workgroups to the XCDs round-robin, and XCD x takes blocks
   // x, x + 8, ... of kBucketBlock consecutive chunks, so the eight XCDs stream through neighbouring
   // 256 KB blocks of one front. The map's tail past the last whole round of blocks keeps plain order
   // (the mapping stays a bijection on the padded map). See kBucketBlock.
-  const uint32_t w = blockIdx.x, full = gridDim.x / (kXcds * kBucketBlock) * (kXcds * kBucketBlock);
+  constexpr uint32_t kTensor = (1u << kMapTensorBits) - 1;
+  const uint32_t w = blockIdx.x, full = n_map / (kXcds * kBucketBlock) * (kXcds * kBucketBlock);
   const uint32_t j = w / kXcds;
   const uint32_t c = w < full ? ((j / kBucketBlock) * kXcds + w % kXcds) * kBucketBlock + j % kBucketBlock : w;
   const uint32_t m = tile_map[c];
+  const uint32_t next = UNPACK && REALIGN ? tile_map[umin(c + 1, n_map - 1)] & kTensor : 0;  // the next chunk's tensor
   if (m == kNoSeg) return;
   const uint32_t r = m >> kMapTensorBits;
-  uint32_t g = m & ((1u << kMapTensorBits) - 1);
+  uint32_t g = m & kTensor;
   const uint64_t c0 = rank_info[4 * r], S = rank_info[4 * r + 1];
   const uint32_t gend = uint32_t(rank_info[4 * r + 2]);
+  // Tensor g's stream range and pointer. A rank's last tensor has no end among its rank's offsets: S stands
+  // in, and what is loaded behind the last offset of all (the rank records) is not used.
+  uint64_t toff = stream_off[g], tnext = stream_off[g + 1];
+  uint64_t tptr = tensor_ptrs[g];
   uint64_t bucket0;
   if (r < uint32_t(kArgRanks)) {
     bucket0 = bases.first[r];
   } else {
     const uint32_t lane = threadIdx.x & 63;
     uint64_t acc = 0;
-    for (uint32_t q = lane; q < r; q += 64) acc += (rank_bytes[q] + B - 1) / B;
+    for (uint32_t q = lane; q < r; q += 64) acc += div_by(rank_bytes[q] + B - 1, B, recip);
     bucket0 = uniform64(wave_sum(acc));
   }
   uint64_t start = (c - c0) * kTileChunkBytes;
   uint64_t end = start + kTileChunkBytes < S ? start + kTileChunkBytes : S;
-  uint64_t k = b_shift >= 0 ? start >> b_shift : start / B;
-  if (realign) {
+  uint64_t k = div_by(start, B, recip);
+  if constexpr (REALIGN) {
     // pack: bucket k's grid starts at stream byte k*B; unpack: a tensor's grid starts at its stream
     // offset (the tensor holding `end` is the next chunk's map entry). A start never leaves its bucket
     // (pack) or tensor (unpack); it may move back into earlier tensors (pack) or an earlier bucket
     // (unpack). Chunks stay non-empty and below 2 * kTileChunkBytes.
     constexpr uint64_t kGrid = kTileChunkBytes - 1;
     if constexpr (UNPACK) {
-      start -= (start - stream_off[g]) & kGrid;
-      if (end < S) end -= (end - stream_off[tile_map[c + 1] & ((1u << kMapTensorBits) - 1)]) & kGrid;
-      k = b_shift >= 0 ? start >> b_shift : start / B;
+      start -= (start - toff) & kGrid;
+      if (end < S) end -= (end - stream_off[next]) & kGrid;
+      k = div_by(start, B, recip);
     } else {
       start -= (start - k * B) & kGrid;
-      if (end < S) end -= (end - end / B * B) & kGrid;
-      while (stream_off[g] > start) --g;
+      if (end < S) end -= (end - div_by(end, B, recip) * B) & kGrid;
+      if (toff > start) {
+        while (stream_off[g] > start) --g;
+        toff = stream_off[g];
+        tnext = stream_off[g + 1];
+        tptr = tensor_ptrs[g];
+      }
     }
   }
   uint64_t kend = (k + 1) * B;
   uint64_t pos = start;
   while (pos < end) {
-    const uint64_t toff = stream_off[g];
-    const uint64_t tend = g + 1 < gend ? stream_off[g + 1] : S;
+    const uint64_t tend = g + 1 < gend ? tnext : S;
     if (tend <= pos) {  // the chunk moves on into the next tensor (or past an empty one)
       ++g;
+      toff = tnext;
+      tnext = stream_off[g + 1];
+      tptr = tensor_ptrs[g];
       continue;
     }
     uint64_t pend = end < tend ? end : tend;
     if (kend < pend) pend = kend;
-    uint8_t* tp = reinterpret_cast<uint8_t*>(tensor_ptrs[g]) + (pos - toff);
+    uint8_t* tp = reinterpret_cast<uint8_t*>(tptr) + (pos - toff);
     uint8_t* bp = reinterpret_cast<uint8_t*>(bucket_ptrs[bucket0 + k]) + (pos - k * B);
     const uint32_t n = uint32_t(pend - pos);
-    if constexpr (UNPACK) wg_copy_bytes<kBucketTileThreads, U, kShiftUnroll, NT, false>(bp, tp, n);
-    else wg_copy_bytes<kBucketTileThreads, U, kShiftUnroll, NT, false>(tp, bp, n);
+    if constexpr (UNPACK) wg_copy<kBucketTileThreads, U, POL>(bp, tp, n, uint32_t(pos - toff) & 15u);
+    else wg_copy<kBucketTileThreads, U, POL>(tp, bp, n, uint32_t(pos - k * B) & 15u);
     pos = pend;
     if (pos == kend) {
       ++k;
@@ -1043,8 +940,7 @@ static int device_cus() {
 // 2 * floor(c / 2) for c >= 2 (c = 1 keeps one). The cap bounds the bytes in flight per CU: on MI355X
 // a copy stream runs fastest with about 24-48 KB in flight per CU and drops by about 8% at 128 KB,
 // where the HBM read/write mix degrades. Automatic (-1): flight / tile_bytes workgroups, at least 2,
-// and no cap from 32 up, with `flight` in destination bytes (see launch_rule).
-constexpr uint64_t kBucketFlightBytes = 64 * 1024;  // pack/unpack: 16 chunks of 4 KB
+// and no cap from 32 up, with `flight` in destination bytes (see launch_rule and bucket_call).
 static size_t occupancy_lds(size_t need, uint64_t tile_bytes, uint64_t flight) {
   int64_t cap = option(EMU_OPT_WG_PER_CU);
   if (cap < 0) {
@@ -1096,6 +992,7 @@ struct LaunchRule {
   uint64_t flight;
 };
 constexpr uint64_t kThroughBytes = 1ull << 30;        // read and written by one reshard launch
+constexpr uint64_t kThroughBucketBytes = 1ull << 29;  // by one pack or unpack
 static LaunchRule launch_rule(const Plan* P, uint32_t groups) {
   const bool any = P->info.n_general_segments > 0;
   const uint64_t moved = (P->info.bytes_read + P->info.bytes_written) * groups;
@@ -1201,29 +1098,40 @@ static int bucket_call(emu_plan_t plan, const void* ws, int32_t side, uint64_t B
       bases.first[r] = acc;
       acc += (s.rank_bytes[r] + B - 1) / B;
     }
-    const int32_t b_shift = (B & (B - 1)) == 0 ? __builtin_ctzll(B) : -1;
-    // chunks are cut on the stream's 16-byte grid unless the destination's grid differs: buckets whose
-    // size is not a multiple of 16 (pack), tensors at stream offsets that are not (unpack)
-    const uint32_t realign = unpack ? uint32_t(!s.offsets_grid) : uint32_t(B % kTileChunkBytes != 0);
+    // chunks are cut on the stream's grid unless the destination's differs: buckets whose size is not a
+    // multiple of 4 KB (pack), tensors at stream offsets that are not (unpack)
+    const bool realign = unpack ? !s.offsets_grid : B % kTileChunkBytes != 0;
     const dim3 g(uint32_t(t.n_tiles));  // padded to a multiple of kXcds
-    const size_t lds = occupancy_lds(0, kTileChunkBytes, kBucketFlightBytes);
+    // Residency and cache policy as for the reshard. 10 / 12 / 16 chunks per CU: 9,537 / 9,738 / 10,087 us for the 8B
+    // pack and unpack, whose chunks end on tensor and bucket ends; 298 / 288 / 292 us where chunks are moved to
+    // the destination's grid and hold several pieces (odd widths), and 168 / 162 / 165 in a set of 0.26 GB. Writing
+    // through took 162 us there against 166 with "nt", 9,537 against 9,907 at 8B, and 100.5 against 99.7 at 0.15 GB.
+    const size_t lds = occupancy_lds(0, kTileChunkBytes, (realign ? 48 : 40) << 10);
+    const bool through = ntm && 2 * s.total_bytes >= kThroughBucketBytes;
+    const uint64_t recip = ~0ull / B;
     drop_pending_error();
-    if (unpack) {
-      if (ntm) hipLaunchKernelGGL((k_buckets_tile<true, true, kBucketTileVecs>), g, dim3(kBucketTileThreads), lds, st, so, ri, rb, tm, B, b_shift, realign, tptr, bptr, bases);
-      else hipLaunchKernelGGL((k_buckets_tile<true, false, kBucketTileVecs>), g, dim3(kBucketTileThreads), lds, st, so, ri, rb, tm, B, b_shift, realign, tptr, bptr, bases);
-    } else {
-      if (ntm) hipLaunchKernelGGL((k_buckets_tile<false, true, kBucketTileVecs>), g, dim3(kBucketTileThreads), lds, st, so, ri, rb, tm, B, b_shift, realign, tptr, bptr, bases);
-      else hipLaunchKernelGGL((k_buckets_tile<false, false, kBucketTileVecs>), g, dim3(kBucketTileThreads), lds, st, so, ri, rb, tm, B, b_shift, realign, tptr, bptr, bases);
-    }
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, g, dim3(kBucketTileThreads), lds, st, tm, uint32_t(t.n_tiles), ri, so, tptr, bptr, B,
+                         recip, rb, bases);
+    };
+    auto by_policy = [&](auto unpacks, auto realigns) {
+      constexpr int U = kBucketTileVecs;
+      constexpr bool kUnpack = decltype(unpacks)::value, kRealign = decltype(realigns)::value;
+      if (through) launch(k_buckets_tile<kUnpack, POL_THROUGH, U, kRealign>);
+      else if (ntm) launch(k_buckets_tile<kUnpack, POL_NT, U, kRealign>);
+      else launch(k_buckets_tile<kUnpack, POL_PLAIN, U, kRealign>);
+    };
+    if (unpack) realign ? by_policy(std::true_type(), std::true_type()) : by_policy(std::true_type(), std::false_type());
+    else realign ? by_policy(std::false_type(), std::true_type()) : by_policy(std::false_type(), std::false_type());
     return hip_check(unpack ? "emu_unpack_buckets launch" : "emu_pack_buckets launch");
   }
   drop_pending_error();
   if (unpack) {
-    if (ntm) hipLaunchKernelGGL((k_buckets<true, true, kBucketUnroll>), dim3(uint32_t(grid)), dim3(kThreads), 0, st, sizes, rf, rb, cf, s.nranks, B, tptr, bptr);
-    else hipLaunchKernelGGL((k_buckets<true, false, kBucketUnroll>), dim3(uint32_t(grid)), dim3(kThreads), 0, st, sizes, rf, rb, cf, s.nranks, B, tptr, bptr);
+    if (ntm) hipLaunchKernelGGL((k_buckets<true, POL_NT, kBucketUnroll>), dim3(uint32_t(grid)), dim3(kThreads), 0, st, sizes, rf, rb, cf, s.nranks, B, tptr, bptr);
+    else hipLaunchKernelGGL((k_buckets<true, POL_PLAIN, kBucketUnroll>), dim3(uint32_t(grid)), dim3(kThreads), 0, st, sizes, rf, rb, cf, s.nranks, B, tptr, bptr);
   } else {
-    if (ntm) hipLaunchKernelGGL((k_buckets<false, true, kBucketUnroll>), dim3(uint32_t(grid)), dim3(kThreads), 0, st, sizes, rf, rb, cf, s.nranks, B, tptr, bptr);
-    else hipLaunchKernelGGL((k_buckets<false, false, kBucketUnroll>), dim3(uint32_t(grid)), dim3(kThreads), 0, st, sizes, rf, rb, cf, s.nranks, B, tptr, bptr);
+    if (ntm) hipLaunchKernelGGL((k_buckets<false, POL_NT, kBucketUnroll>), dim3(uint32_t(grid)), dim3(kThreads), 0, st, sizes, rf, rb, cf, s.nranks, B, tptr, bptr);
+    else hipLaunchKernelGGL((k_buckets<false, POL_PLAIN, kBucketUnroll>), dim3(uint32_t(grid)), dim3(kThreads), 0, st, sizes, rf, rb, cf, s.nranks, B, tptr, bptr);
   }
   return hip_check(unpack ? "emu_unpack_buckets launch" : "emu_pack_buckets launch");
 }
