@@ -120,11 +120,12 @@ class EmuError(RuntimeError):
 
 
 _lib = None
+_raw_stream = _current_device = _int64 = None  # torch's, set by load()
 
 
 def load(path: str = LIB_PATH):
     """Load libemu.so (once). Raises if it has not been built: there is no other implementation."""
-    global _lib
+    global _lib, _raw_stream, _current_device, _int64
     if _lib is not None:
         return _lib
     if not os.path.exists(path):
@@ -134,8 +135,11 @@ def load(path: str = LIB_PATH):
     # dependency; loaded after libemu.so, torch would bring in a second HIP runtime in the same process,
     # and the first one to lose the device reports none. The binding's buffers and streams are torch's, so
     # torch's runtime is the one to share.
-    import torch  # noqa: F401
+    import torch
     lib = ctypes.CDLL(path)
+    _int64 = torch.int64
+    if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+        _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
     P, V, I32, I64, U64 = ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64
     sig = {
         "emu_version": ([], ctypes.c_int),
@@ -246,11 +250,16 @@ def layout_check(lay: Layout) -> int:
 
 
 def _stream_handle(stream):
+    """The HIP stream handle of `stream`, or of torch's current stream on the current device. The handle
+    is asked for directly: torch.cuda.current_stream() builds a Stream object first, 2.9 us of the 8.2 us that a
+    reshard call of a tiny model took on the host (0.3 us this way, where torch has these calls)."""
     import torch
 
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 class ShardSet:
@@ -480,45 +489,46 @@ class Plan:
         return [b.view(-1).view(_uint8()) for b in buffers], ptr_table(buffers, device)
 
     def reshard(self, ws, src_ptrs, dst_ptrs, stream=None):
-        self._tables(ws, (src_ptrs, self._n[0], "src_ptrs"), (dst_ptrs, self._n[1], "dst_ptrs"))
-        check(load().emu_reshard(self._h, ctypes.c_void_p(ws.data_ptr()), ctypes.c_void_p(src_ptrs.data_ptr()),
-                                 ctypes.c_void_p(dst_ptrs.data_ptr()), _stream_handle(stream)))
+        w = self._tables(ws, (src_ptrs, self._n[0], "src_ptrs"), (dst_ptrs, self._n[1], "dst_ptrs"))
+        check(load().emu_reshard(self._h, w, src_ptrs.data_ptr(), dst_ptrs.data_ptr(), _stream_handle(stream)))
 
     def reshard_groups(self, ws, src_tables, dst_tables, stream=None):
         """``emu_reshard_groups``: one launch over several shard sets of this plan's layouts. src_tables
         and dst_tables are int64 device tensors holding the groups' pointer tables back to back
         (``group_tables``)."""
-        ns, nd = self.info["n_src_tensors"], self.info["n_dst_tensors"]
+        ns, nd = self._n
         n = src_tables.numel() // ns if ns else 0
-        self._tables(ws, (src_tables, n * ns, "src_tables"), (dst_tables, n * nd, "dst_tables"))
-        check(load().emu_reshard_groups(self._h, ctypes.c_void_p(ws.data_ptr()), n,
-                                        ctypes.c_void_p(src_tables.data_ptr()), ctypes.c_void_p(dst_tables.data_ptr()),
+        w = self._tables(ws, (src_tables, n * ns, "src_tables"), (dst_tables, n * nd, "dst_tables"))
+        check(load().emu_reshard_groups(self._h, w, n, src_tables.data_ptr(), dst_tables.data_ptr(),
                                         _stream_handle(stream)))
 
     def reshard_noalloc(self, src_ptrs, dst_ptrs, stream=None):
         """``emu_reshard_noalloc``: the reshard with the plan tables in the library's static device array
         (no workspace; nothing allocated by the call)."""
-        self._tables(None, (src_ptrs, self.info["n_src_tensors"], "src_ptrs"),
-                     (dst_ptrs, self.info["n_dst_tensors"], "dst_ptrs"))
-        check(load().emu_reshard_noalloc(self._h, ctypes.c_void_p(src_ptrs.data_ptr()),
-                                         ctypes.c_void_p(dst_ptrs.data_ptr()), _stream_handle(stream)))
+        self._tables(None, (src_ptrs, self._n[0], "src_ptrs"), (dst_ptrs, self._n[1], "dst_ptrs"))
+        check(load().emu_reshard_noalloc(self._h, src_ptrs.data_ptr(), dst_ptrs.data_ptr(), _stream_handle(stream)))
 
     def _tables(self, ws, *tables):
         """Refuse, before any library call, pointer tables the kernels would read past the end of:
-        each must be an int64 device tensor with exactly the entries the plan indexes."""
+        each must be an int64 device tensor with exactly the entries the plan indexes. Returns the
+        workspace's address (None without a workspace)."""
         for t, n, what in tables:
-            if str(getattr(t, "dtype", None)) != "torch.int64":
+            dtype = getattr(t, "dtype", None)
+            if dtype is not _int64 and str(dtype) != "torch.int64":
                 raise ValueError(f"{what} must be an int64 tensor (emu.ptr_table), not {type(t).__name__}")
             if t.numel() != n or (n and not t.is_contiguous()):
                 raise ValueError(f"{what} has {t.numel()} entries, the plan needs {n} (contiguous)")
         for t, _, what in tables:
             if not t.is_cuda:
                 raise ValueError(f"{what} must be a device tensor")
-        if ws is not None:
-            if not getattr(ws, "is_cuda", False):
-                raise ValueError("the workspace must be a device tensor")
-            if ws.data_ptr() not in self._uploads:
-                raise EmuError(-5, f"workspace at {ws.data_ptr():#x} holds no upload of this plan (Plan.upload)")
+        if ws is None:
+            return None
+        if not getattr(ws, "is_cuda", False):
+            raise ValueError("the workspace must be a device tensor")
+        w = ws.data_ptr()
+        if w not in self._uploads:
+            raise EmuError(-5, f"workspace at {w:#x} holds no upload of this plan (Plan.upload)")
+        return w
 
     def _bucket_tables(self, ws, side, bucket_bytes, tensor_ptrs, bucket_ptrs):
         if side not in (0, 1):
@@ -529,20 +539,18 @@ class Plan:
         if nb is None:
             es = ESIZE[DTYPES[(self.src if side == 0 else self.dst).dtype]]
             if bucket_bytes == 0 or bucket_bytes % es:
-                return  # the library refuses the size (EMU_ERR_BUCKET) before launching anything
+                return ws.data_ptr()  # the library refuses the size (EMU_ERR_BUCKET) before launching anything
             nb = self._nbuckets[(side, bucket_bytes)] = self.bucket_layout(side, bucket_bytes, -1)[0]
-        self._tables(ws, (tensor_ptrs, self._n[side], "tensor_ptrs"), (bucket_ptrs, nb, "bucket_ptrs"))
+        return self._tables(ws, (tensor_ptrs, self._n[side], "tensor_ptrs"), (bucket_ptrs, nb, "bucket_ptrs"))
 
     def pack(self, ws, side, bucket_bytes, tensor_ptrs, bucket_ptrs, stream=None):
-        self._bucket_tables(ws, side, bucket_bytes, tensor_ptrs, bucket_ptrs)
-        check(load().emu_pack_buckets(self._h, ctypes.c_void_p(ws.data_ptr()), side, bucket_bytes,
-                                      ctypes.c_void_p(tensor_ptrs.data_ptr()), ctypes.c_void_p(bucket_ptrs.data_ptr()),
+        w = self._bucket_tables(ws, side, bucket_bytes, tensor_ptrs, bucket_ptrs)
+        check(load().emu_pack_buckets(self._h, w, side, bucket_bytes, tensor_ptrs.data_ptr(), bucket_ptrs.data_ptr(),
                                       _stream_handle(stream)))
 
     def unpack(self, ws, side, bucket_bytes, bucket_ptrs, tensor_ptrs, stream=None):
-        self._bucket_tables(ws, side, bucket_bytes, tensor_ptrs, bucket_ptrs)
-        check(load().emu_unpack_buckets(self._h, ctypes.c_void_p(ws.data_ptr()), side, bucket_bytes,
-                                        ctypes.c_void_p(bucket_ptrs.data_ptr()), ctypes.c_void_p(tensor_ptrs.data_ptr()),
+        w = self._bucket_tables(ws, side, bucket_bytes, tensor_ptrs, bucket_ptrs)
+        check(load().emu_unpack_buckets(self._h, w, side, bucket_bytes, bucket_ptrs.data_ptr(), tensor_ptrs.data_ptr(),
                                         _stream_handle(stream)))
 
     # -- host-side table checks ------------------------------------------------------------------
