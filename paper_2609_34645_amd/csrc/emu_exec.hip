@@ -471,6 +471,43 @@ __device__ __forceinline__ void tile_any(const uint8_t* s, uint8_t* d, uint32_t 
   }
 }
 
+// A whole tile of units inside one row: aligned at d, at any element of the source, nothing to cut and no lane
+// masked. It is what lets such plans write through (see launch_rule); by itself it gained under 1%.
+template <int U, int POL, bool ZERO, int CVT>
+__device__ __forceinline__ void tile_inner(const uint8_t* s, uint8_t* d) {
+  constexpr uint32_t D = ZERO ? 16u : any_unit_bytes(CVT);
+  constexpr int N = U * 16 / int(D), P = N > 8 ? 8 : N;
+  const uint32_t tid = threadIdx.x;
+#pragma unroll
+  for (int b = 0; b < N; b += P) {
+    v4u r[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const uint32_t from = any_src<CVT>(((b + k) * kReshardThreads + tid) * D);
+      if constexpr (ZERO) {
+        r[k] = v4u{0, 0, 0, 0};
+      } else if constexpr (CVT == CVT_BF16_F32) {
+        const v2u h = ld8_any<POL>(s, from);
+        r[k].x = h.x;
+        r[k].y = h.y;
+      } else {
+        r[k] = ld16_any<POL>(s, from);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const uint32_t to = ((b + k) * kReshardThreads + tid) * D;
+      if constexpr (CVT == CVT_F32_BF16 && !ZERO) {
+        st8<POL>(d, to, to_bf16x4(r[k]));
+      } else if constexpr (CVT == CVT_BF16_F32 && !ZERO) {
+        st16<POL>(d, to, v4u{r[k].x << 16, r[k].x & 0xffff0000u, r[k].y << 16, r[k].y & 0xffff0000u});
+      } else {
+        st16<POL>(d, to, r[k]);
+      }
+    }
+  }
+}
+
 // Rows shorter than a unit (narrow column slices, the ends of bucket-cut rows): element by element, one per
 // lane and step, in row-major order.
 template <int U, bool ZERO, int CVT>
@@ -530,11 +567,19 @@ __device__ __forceinline__ void run_tile(const DevSeg& g, uint64_t lt, const uin
     move_run<U, POL, ZERO, LDS, CVT>(s, d, cnt, stage);
   } else if (mode == SEG_ANY_FLAT) {
     constexpr uint32_t D = ZERO ? 16u : any_unit_bytes(CVT), TU = uint32_t(TV) * 16 / D;  // units per tile
-    const uint32_t n0 = uint32_t(lt) * TU, q0 = g.rv > 1 ? __umulhi(n0, g.magic) : n0;
-    tile_any<U, POL, ZERO, CVT, true>(ZERO ? nullptr : sb + g.src_off + uint64_t(q0) * g.src_stride,
-                                     db + g.dst_off + uint64_t(q0) * g.dst_stride, n0 - q0 * g.rv,
-                                     umin(g.param - n0, TU), g.rv, g.magic, uint32_t(g.src_stride),
-                                     uint32_t(g.dst_stride), g.mode >> SEG_GRID_SHIFT, 0, int32_t(g.run) - int32_t(D));
+    const uint32_t n0 = uint32_t(lt) * TU, q0 = g.rv > 1 ? __umulhi(n0, g.magic) : n0, r0 = n0 - q0 * g.rv;
+    const uint32_t gmask = g.mode >> SEG_GRID_SHIFT;
+    const uint8_t* s = ZERO ? nullptr : sb + g.src_off + uint64_t(q0) * g.src_stride;
+    uint8_t* d = db + g.dst_off + uint64_t(q0) * g.dst_stride;
+    // A row's first unit on the grid is among its first 128 bytes of units, and its last among the last 256:
+    // a row has up to gmask + 15 bytes more of units than of data, rounded up to the grid.
+    if (r0 * D >= 128 && (r0 + TU) * D + 256 <= g.rv * D) {
+      const uint32_t at = r0 * D - (uint32_t(reinterpret_cast<uintptr_t>(d)) & gmask);
+      tile_inner<U, POL, ZERO, CVT>(s + any_src<CVT>(at), d + at);
+    } else {
+      tile_any<U, POL, ZERO, CVT, true>(s, d, r0, umin(g.param - n0, TU), g.rv, g.magic, uint32_t(g.src_stride),
+                                        uint32_t(g.dst_stride), gmask, 0, int32_t(g.run) - int32_t(D));
+    }
   } else if (mode == SEG_ANY_CHUNK) {
     // Slice ch of a row is its bytes [ch * TB - m, (ch + 1) * TB - m), cut to the row, with m the phase of the
     // row's address on the grid; the last slice also takes what is left (up to gmask bytes).
@@ -546,9 +591,13 @@ __device__ __forceinline__ void run_tile(const DevSeg& g, uint64_t lt, const uin
     uint8_t* d = db + g.dst_off + row * g.dst_stride + b0;
     const uint32_t gmask = g.mode >> SEG_GRID_SHIFT;
     const int32_t m = int32_t(uint32_t(reinterpret_cast<uintptr_t>(d)) & gmask);
-    const int32_t end = ch + 1 == g.param ? int32_t(g.run - b0) : TB - m;
-    tile_any<U, POL, ZERO, CVT, false>(s, d, 0, (uint32_t(end + m) + D - 1) / D, 0, 0, 0, 0, gmask, ch ? -m : 0,
-                                      end - int32_t(D));
+    if (ch != 0 && ch + 1 != g.param) {
+      tile_inner<U, POL, ZERO, CVT>(s - any_src<CVT>(uint32_t(m)), d - m);
+    } else {
+      const int32_t end = ch + 1 == g.param ? int32_t(g.run - b0) : TB - m;
+      tile_any<U, POL, ZERO, CVT, false>(s, d, 0, (uint32_t(end + m) + D - 1) / D, 0, 0, 0, 0, gmask, ch ? -m : 0,
+                                         end - int32_t(D));
+    }
   } else {
     tile_elems<U, ZERO, CVT>(g, lt, sb, db);
   }
@@ -984,9 +1033,10 @@ struct Tables {
 //    on the odd widths. bf16 -> fp32, which reads half: written through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 /
 //    1372 us (1B, fused to separate formats), otherwise 48 KB, 10 / 12 / 14 / 16 tiles in 1414 / 1382 / 1394 / 1418.
 //  - Cache policy. Writing through gains from about 1 GB moved per launch on (1B copy 890 against 914 us, 8B 4823
-//    against 4928, fp32 -> bf16 1319 against 1335, bf16 -> fp32 1364 against 1382), not below (0.7 GB: 107.2 against
-//    105.5; 4 MB: 2.7 against 2.5), and not where units at any alignment end on lines that a neighbour completes (odd
-//    widths, 1.6 GB: 280 against 272).
+//    against 4928, fp32 -> bf16 1319 against 1335, bf16 -> fp32 1364 against 1382; copies with units at any alignment:
+//    odd widths, 4.8 GB, 724 against 743, 8B into and out of odd buckets 10.12 against 10.28 ms), not below (0.7 GB:
+//    107.2 against 105.5; 4 MB: 2.7 against 2.5), and not for conversions at any alignment (218 against 216, bf16 ->
+//    fp32 785 against 758).
 struct LaunchRule {
   int policy;
   uint64_t flight;
@@ -997,7 +1047,8 @@ static LaunchRule launch_rule(const Plan* P, uint32_t groups) {
   const bool any = P->info.n_general_segments > 0;
   const uint64_t moved = (P->info.bytes_read + P->info.bytes_written) * groups;
   LaunchRule r{POL_PLAIN, 48 << 10};
-  if (option(EMU_OPT_NONTEMPORAL) != 0) r.policy = !any && moved >= kThroughBytes ? POL_THROUGH : POL_NT;
+  if (option(EMU_OPT_NONTEMPORAL) != 0)
+    r.policy = moved >= kThroughBytes && (!any || P->cvt == CVT_NONE) ? POL_THROUGH : POL_NT;
   if (P->cvt == CVT_F32_BF16) r.flight = (any ? 40 : 24) << 10;
   else if (P->cvt == CVT_BF16_F32 && r.policy == POL_THROUGH) r.flight = 56 << 10;
   return r;
