@@ -3,9 +3,9 @@
 // bucket stream tables in its workspace at upload, and the C ABI entry points that launch them.
 //
 // Both kernels are pure HBM streams: no arithmetic on the data (fp32 <-> bf16 conversion aside),
-// integer address math only. Every thread moves 16-byte vectors (global_load/store_dwordx4), a tile is
+// integer address math only. Every thread moves 16-byte vectors, from and to any element address, a tile is
 // threads * U vectors, and all U loads of a tile are issued before its stores. How many tiles are
-// resident per CU is bounded (EMU_OPT_WG_PER_CU), so that each CU keeps 48-64 KB of loads in flight:
+// resident per CU is bounded (EMU_OPT_WG_PER_CU), so that each CU keeps 24-56 KB of tiles in flight:
 // enough to cover HBM latency, and few enough that the mixed read/write stream does not congest. Both
 // tile kernels run one wave64 per workgroup, so that each tile's address computation (map entry,
 // descriptor or rank record, pointers) is done once rather than once per wave.
@@ -1157,7 +1157,9 @@ static int bucket_call(emu_plan_t plan, const void* ws, int32_t side, uint64_t B
     // pack and unpack, whose chunks end on tensor and bucket ends; 298 / 288 / 292 us where chunks are moved to
     // the destination's grid and hold several pieces (odd widths), and 168 / 162 / 165 in a set of 0.26 GB. Writing
     // through took 162 us there against 166 with "nt", 9,537 against 9,907 at 8B, and 100.5 against 99.7 at 0.15 GB.
-    const size_t lds = occupancy_lds(0, kTileChunkBytes, (realign ? 48 : 40) << 10);
+    // Buckets that start inside a dword make the unpack's loads slower: 12 per CU there too (8B at 2^28 - 2:
+    // 4,838 us against 4,943 at 10; at 2^28 - 4: 4,792 against 4,797).
+    const size_t lds = occupancy_lds(0, kTileChunkBytes, (realign || B % 4 != 0 ? 48 : 40) << 10);
     const bool through = ntm && 2 * s.total_bytes >= kThroughBucketBytes;
     const uint64_t recip = ~0ull / B;
     drop_pending_error();
