@@ -671,11 +671,11 @@ static int finalize(Plan& P) {
     P.dsegs.push_back(d);
   }
   P.ntiles = tiles;
-  // Tile map: the copy segments' tiles, then the zero-fill segments' tiles, which run on their own
-  // kernel instance. Each section is padded with kNoSeg to a whole number of XCD groups, so that every
-  // workgroup of a grid (a multiple of kXcdCount) reads an entry of its own section and the kernel
-  // needs no bounds check before its first load. Here each segment gets its first map index; the
-  // upload's k_tile_map writes the map on the device from those indices and the tile counts.
+  // Tile map: the copy segments' tiles, then the zero-fill segments' tiles, run by one launch. Each section
+  // is padded with kNoSeg to a whole number of XCD groups, so that every workgroup of the grid (a multiple of
+  // kXcdCount) reads an entry of the map and the kernel needs no bounds check before its first load. Here
+  // each segment gets its first map index; the upload's k_tile_map writes the map on the device from those
+  // indices and the tile counts.
   uint64_t nmap = 0;
   for (int pass = 0; pass < 2; ++pass) {
     if (pass == 1) P.zero_tile0 = nmap;
