@@ -171,7 +171,23 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 // it waits for the tile's first stores to complete before it issues the last ones. A tile without masked
 // stores needs no such wait, which is why full tiles have paths of their own below. At 6 resident tiles per
 // CU the 1B TP4 -> TP2 reshard took 957 us with both, 1,086 us before; at 8 per CU 926 against 962.
-__device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
+//
+// The loaded values pass through the (empty) statements: a load that only a guarded store uses is otherwise
+// moved into that store's block, behind the wait, where it takes a second memory latency. With a plain s_waitcnt
+// here, reshard + pack + unpack of the tiny decoder (4 MB, replayed in a graph) took 14.4 us in bf16 and 17.6 in
+// fp32; without any wait 13.3 and 15.9; this way 12.6 and 15.1.
+__device__ __forceinline__ void arrived(v4u& a) { asm volatile("" : "+v"(a)); }
+__device__ __forceinline__ void arrived(v2u& a) { asm volatile("" : "+v"(a)); }
+template <int CVT>
+__device__ __forceinline__ void arrived(Raw<CVT>& r) {
+  arrived(r.a);
+  if constexpr (CVT == CVT_F32_BF16) arrived(r.b);
+}
+template <typename T, int N>
+__device__ __forceinline__ void loads_done(T (&r)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) arrived(r[k]);
+}
 
 // Workgroup-cooperative copy of n > 0 bytes between any even addresses (n < 2^31). The body runs in 16-byte
 // units on the destination's 16-byte grid; the first and the last unit are moved inward to the copy's ends
@@ -200,7 +216,7 @@ __device__ __forceinline__ void wg_copy(const uint8_t* __restrict__ s, uint8_t* 
         at[k] = umin(x < m ? 0u : x - m, n - 16u);
         r[k] = ld16_any<POL>(s, at[k]);
       }
-      loads_done();
+      loads_done(r);
 #pragma unroll
       for (int k = 0; k < P; ++k)
         if (b + k * NTH + tid < cnt) st16_any<POL>(d, at[k], r[k]);
@@ -267,7 +283,7 @@ __device__ __forceinline__ void tile_rows(const uint8_t* s, uint8_t* d, uint32_t
       const uint32_t q = rv > 1 ? __umulhi(n, mg) : n;
       raw[u] = ld_raw<CVT, POL>(s, q * ss + (n - q * rv) * kSrcVecBytes<CVT>);
     }
-    if constexpr (!FULL) loads_done();
+    if constexpr (!FULL) loads_done(raw);
 #pragma unroll
     for (int u = 0; u < U; ++u) r[u] = cook<CVT>(raw[u]);
   }
@@ -297,7 +313,7 @@ __device__ __forceinline__ void tile_run(const uint8_t* s, uint8_t* d, uint32_t 
       const uint32_t i = u * kReshardThreads + tid;
       raw[u] = ld_raw<CVT, POL>(s, (FULL ? i : umin(i, last)) * kSrcVecBytes<CVT>);
     }
-    if constexpr (!FULL) loads_done();
+    if constexpr (!FULL) loads_done(raw);
 #pragma unroll
     for (int u = 0; u < U; ++u) r[u] = cook<CVT>(raw[u]);
   }
@@ -336,7 +352,7 @@ __device__ __forceinline__ void tile_run_f32_bf16(const uint8_t* s, uint8_t* d, 
       const uint32_t i = (h * 2 * P + k) * kReshardThreads + tid;
       a[k] = ld16<POL>(s, (FULL ? i : umin(i, last)) * 16u);
     }
-    if constexpr (!FULL) loads_done();
+    if constexpr (!FULL) loads_done(a);
 #pragma unroll
     for (int k = 0; k < 2 * P; ++k) {
       const uint32_t i = (h * 2 * P + k) * kReshardThreads + tid;
@@ -363,7 +379,7 @@ __device__ __forceinline__ void tile_rows_f32_bf16(const uint8_t* s, uint8_t* d,
       const uint32_t q = rv > 1 ? __umulhi(n >> 1, mg) : (n >> 1);
       a[k] = ld16<POL>(s, q * ss + (n - q * h) * 16u);
     }
-    if constexpr (!FULL) loads_done();
+    if constexpr (!FULL) loads_done(a);
 #pragma unroll
     for (int k = 0; k < 2 * P; ++k) {
       const uint32_t i = (p * 2 * P + k) * kReshardThreads + tid;
@@ -434,7 +450,7 @@ __device__ __forceinline__ void tile_any(const uint8_t* s, uint8_t* d, uint32_t 
   for (uint32_t b = 0; b < cnt; b += uint32_t(kReshardThreads) * P) {  // one pass, two for a run's longer last tile
     uint32_t to[P];
     bool live[P];
-    v4u r[P];
+    std::conditional_t<CVT == CVT_BF16_F32 && !ZERO, v2u, v4u> r[P];
 #pragma unroll
     for (int k = 0; k < P; ++k) {
       const uint32_t i = b + k * kReshardThreads + tid, n = r0 + umin(i, cnt - 1);
@@ -449,14 +465,12 @@ __device__ __forceinline__ void tile_any(const uint8_t* s, uint8_t* d, uint32_t 
       if constexpr (ZERO) {
         r[k] = v4u{0, 0, 0, 0};
       } else if constexpr (CVT == CVT_BF16_F32) {
-        const v2u h = ld8_any<POL>(s, from);
-        r[k].x = h.x;
-        r[k].y = h.y;
+        r[k] = ld8_any<POL>(s, from);
       } else {
         r[k] = ld16_any<POL>(s, from);
       }
     }
-    if constexpr (!ZERO) loads_done();
+    if constexpr (!ZERO) loads_done(r);
 #pragma unroll
     for (int k = 0; k < P; ++k) {
       if (!live[k]) continue;
