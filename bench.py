@@ -30,7 +30,7 @@ TINY = (2, 256, 4, 64, 2, 688, 1024)
 ONE_B = (16, 2048, 32, 64, 8, 8192, 128256)
 PMC_SUMMARY = os.path.join(ROOT, "profiles", "reshard_8b_tp2pp2_tp4pp1_pmc.txt")
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2609_34645_amd", "csrc", f)
-               for f in ("emu_exec.hip", "emu_internal.h", "emu_plan.cpp")]
+               for f in ("emu_exec.hip", "emu_internal.h", "emu_plan.cpp", "emu_launch.cpp")]
 
 
 def log(*a):
@@ -44,8 +44,8 @@ def code_only(text):
 
 
 def kernel_hash(texts=None):
-    """Hash of the code that decides the kernels' HBM traffic: the kernels and the plan compiler that
-    lays out their tiles and tables (comments excluded)."""
+    """Hash of the code that decides the kernels' HBM traffic: the kernels, the plan compiler that lays
+    out their tiles and tables, and the rules they are launched by (comments excluded)."""
     if texts is None:
         texts = [open(p).read() for p in KERNEL_SRCS]
     return hashlib.sha256("\n".join(code_only(t) for t in texts).encode()).hexdigest()[:16]

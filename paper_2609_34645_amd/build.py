@@ -1,8 +1,8 @@
 """Build libemu.so in-tree for gfx950 with hipcc.
 
-Run as ``python -m paper_2609_34645_amd.build``. The host plan compiler (emu_plan.cpp) and the HIP
-executor (emu_exec.hip) are compiled to objects under csrc/_build and linked into
-``paper_2609_34645_amd/libemu.so``. Every call rebuilds from source.
+Run as ``python -m paper_2609_34645_amd.build``. The host code (plan compiler emu_plan.cpp,
+planner emu_transition.cpp, launch rules emu_launch.cpp) and the HIP executor (emu_exec.hip) are compiled to
+objects under csrc/_build and linked into ``paper_2609_34645_amd/libemu.so``. Every call rebuilds from source.
 """
 from __future__ import annotations
 
@@ -39,7 +39,8 @@ def _run(cmd, verbose):
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     objs = []
-    for src, lang in (("emu_plan.cpp", "c++"), ("emu_transition.cpp", "c++"), ("emu_exec.hip", "hip")):
+    for src, lang in (("emu_plan.cpp", "c++"), ("emu_transition.cpp", "c++"), ("emu_launch.cpp", "c++"),
+                      ("emu_exec.hip", "hip")):
         obj = os.path.join(BUILD, src + ".o")
         _run([HIPCC, "-x", lang, *HIP_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
         objs.append(obj)

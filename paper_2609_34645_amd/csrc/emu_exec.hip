@@ -32,14 +32,13 @@ typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v4u gv4u;
 typedef __attribute__((address_space(1))) uint8_t gu8;
 
-// Cache policies of the kernels' loads and stores. POL_NT and POL_THROUGH load with "nt" (streaming).
+// Cache policies of the kernels' loads and stores (enum Policy). POL_NT and POL_THROUGH load with "nt" (streaming).
 // POL_NT also stores with it; POL_THROUGH stores with "sc1 nt", as buffer stores: written through to memory
 // as they come, instead of staying in the XCD's L2 until evicted. With as many tiles in flight as the
 // reshard needs to cover its tables' latency, write-through holds HBM's read/write mix better: a bare
 // 4 KB-tile copy of 8 GB at 8 / 10 resident waves per CU ran at 6.71 / 6.55 TB/s against 6.52 / 6.28 with
-// "nt" (6.80 / 6.73 at 6), the 8B reshard at 10 per CU in 4.80 ms against 4.93. Each plan's choice is made
-// where it is launched.
-enum Policy : int { POL_PLAIN = 0, POL_NT = 1, POL_THROUGH = 2 };
+// "nt" (6.80 / 6.73 at 6), the 8B reshard at 10 per CU in 4.80 ms against 4.93. Which call takes which:
+// emu_launch.cpp.
 constexpr int kThroughBits = 2 | 16;  // nt | sc1
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t whole_range(uint8_t* base) {
   return __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000);  // raw, unswizzled, 2^32 - 1 bytes
@@ -486,7 +485,7 @@ __device__ __forceinline__ void tile_any(const uint8_t* s, uint8_t* d, uint32_t 
 }
 
 // A whole tile of units inside one row: aligned at d, at any element of the source, nothing to cut and no lane
-// masked. It is what lets such plans write through (see launch_rule); by itself it gained under 1%.
+// masked. It is what lets such plans write through (see reshard_rule); by itself it gained under 1%.
 template <int U, int POL, bool ZERO, int CVT>
 __device__ __forceinline__ void tile_inner(const uint8_t* s, uint8_t* d) {
   constexpr uint32_t D = ZERO ? 16u : any_unit_bytes(CVT);
@@ -996,20 +995,11 @@ static int device_cus() {
   return v > 0 ? v : -1;
 }
 
-// Dynamic LDS for a tile kernel that needs `need` bytes and moves `tile_bytes` per workgroup pass.
-// A residency cap of c workgroups per CU (EMU_OPT_WG_PER_CU) is enforced by reserving the CU's LDS
-// divided by c, rounded down to whole KB; the kernels never touch the reserved bytes. The CU's LDS is
-// allocated in two halves and a workgroup's block lies in one half, so the resident count is
-// 2 * floor(c / 2) for c >= 2 (c = 1 keeps one). The cap bounds the bytes in flight per CU: on MI355X
-// a copy stream runs fastest with about 24-48 KB in flight per CU and drops by about 8% at 128 KB,
-// where the HBM read/write mix degrades. Automatic (-1): flight / tile_bytes workgroups, at least 2,
-// and no cap from 32 up, with `flight` in destination bytes (see launch_rule and bucket_call).
-static size_t occupancy_lds(size_t need, uint64_t tile_bytes, uint64_t flight) {
-  int64_t cap = option(EMU_OPT_WG_PER_CU);
-  if (cap < 0) {
-    cap = int64_t(flight / (tile_bytes ? tile_bytes : 1));
-    cap = cap < 2 ? 2 : cap >= 32 ? 0 : cap;
-  }
+// Dynamic LDS for a tile kernel that needs `need` bytes. A residency cap of `cap` workgroups per CU is
+// enforced by reserving the CU's LDS divided by cap, rounded down to whole KB; the kernels never touch the
+// reserved bytes. The CU's LDS is allocated in two halves and a workgroup's block lies in one half, so the
+// resident count is 2 * floor(cap / 2) for cap >= 2 (1 keeps one).
+static size_t occupancy_lds(size_t need, int cap) {
   if (cap == 0) return need;
   const int per_cu = device_attr(hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, 1);
   const int per_wg = device_attr(hipDeviceAttributeMaxSharedMemoryPerBlock, 2);
@@ -1038,42 +1028,13 @@ struct Tables {
   uint32_t groups, src_n, dst_n;
 };
 
-// How a plan's reshard is launched, from what it moves. Measured at 4 KB tiles, several settings in one process
-// on the same buffers, with the states in rotation that no cache holds:
-//  - Residency (flight, destination bytes in flight per CU). Copies: 48 KB; 8 / 10 / 12 / 14 tiles ran the 1B
-//    TP4 -> TP2 reshard in 912 / 890 / 890 / 900 us and a decoder with odd widths in 155 / 147 / 145 / 148.
-//    fp32 -> bf16, which reads twice what it writes: 24 KB; 4 / 6 / 8 / 10 tiles took 1548 / 1319 / 1340 / 1355 us
-//    on aligned 1B shards; with units at any alignment, whose address work is longer, 40 KB: 285 / 226 / 217 / 216
-//    on the odd widths. bf16 -> fp32, which reads half: written through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 /
-//    1372 us (1B, fused to separate formats), otherwise 48 KB, 10 / 12 / 14 / 16 tiles in 1414 / 1382 / 1394 / 1418.
-//  - Cache policy. Writing through gains from about 1 GB moved per launch on (1B copy 890 against 914 us, 8B 4823
-//    against 4928, fp32 -> bf16 1319 against 1335, bf16 -> fp32 1364 against 1382; copies with units at any alignment:
-//    odd widths, 4.8 GB, 724 against 743, 8B into and out of odd buckets 10.12 against 10.28 ms), not below (0.7 GB:
-//    107.2 against 105.5; 4 MB: 2.7 against 2.5), and not for conversions at any alignment (218 against 216, bf16 ->
-//    fp32 785 against 758).
-struct LaunchRule {
-  int policy;
-  uint64_t flight;
-};
-constexpr uint64_t kThroughBytes = 1ull << 30;        // read and written by one reshard launch
-constexpr uint64_t kThroughBucketBytes = 1ull << 29;  // by one pack or unpack
-static LaunchRule launch_rule(const Plan* P, uint32_t groups) {
-  const bool any = P->info.n_general_segments > 0;
-  const uint64_t moved = (P->info.bytes_read + P->info.bytes_written) * groups;
-  LaunchRule r{POL_PLAIN, 48 << 10};
-  if (option(EMU_OPT_NONTEMPORAL) != 0)
-    r.policy = moved >= kThroughBytes && (!any || P->cvt == CVT_NONE) ? POL_THROUGH : POL_NT;
-  if (P->cvt == CVT_F32_BF16) r.flight = (any ? 40 : 24) << 10;
-  else if (P->cvt == CVT_BF16_F32 && r.policy == POL_THROUGH) r.flight = 56 << 10;
-  return r;
-}
-
 // Launches k_reshard over the whole map (n_map entries, a multiple of kXcds) for every group (grid row y =
 // group y).
 struct ReshardLaunch {
   const DevSeg* segs;
   const uint32_t* tm;
-  uint64_t n_map, flight;
+  uint64_t n_map;
+  int cap;
   Tables tb;
   hipStream_t st;
 };
@@ -1081,7 +1042,7 @@ struct ReshardLaunch {
 template <int U, int POL, bool LDS, bool XCD, int CVT>
 static void launch_reshard(const ReshardLaunch& l) {
   constexpr uint64_t kTile = uint64_t(kReshardThreads) * U * 16;
-  const size_t lds = occupancy_lds(LDS ? size_t(kTile) : 0, kTile, l.flight);
+  const size_t lds = occupancy_lds(LDS ? size_t(kTile) : 0, l.cap);
   // a multiple of kXcds whose work-items (64 per workgroup) stay below 2^32 in the grid's x dimension
   constexpr uint64_t kMaxGrid = (1ull << 26) - kXcds;
   for (uint64_t done = 0; done < l.n_map; done += kMaxGrid) {
@@ -1163,18 +1124,10 @@ static int bucket_call(emu_plan_t plan, const void* ws, int32_t side, uint64_t B
       bases.first[r] = acc;
       acc += (s.rank_bytes[r] + B - 1) / B;
     }
-    // chunks are cut on the stream's grid unless the destination's differs: buckets whose size is not a
-    // multiple of 4 KB (pack), tensors at stream offsets that are not (unpack)
-    const bool realign = unpack ? !s.offsets_grid : B % kTileChunkBytes != 0;
+    const bool realign = chunks_realign(s, B, unpack);
+    const LaunchRule rule = bucket_rule(s, B, unpack);
     const dim3 g(uint32_t(t.n_tiles));  // padded to a multiple of kXcds
-    // Residency and cache policy as for the reshard. 10 / 12 / 16 chunks per CU: 9,537 / 9,738 / 10,087 us for the 8B
-    // pack and unpack, whose chunks end on tensor and bucket ends; 298 / 288 / 292 us where chunks are moved to
-    // the destination's grid and hold several pieces (odd widths), and 168 / 162 / 165 in a set of 0.26 GB. Writing
-    // through took 162 us there against 166 with "nt", 9,537 against 9,907 at 8B, and 100.5 against 99.7 at 0.15 GB.
-    // Buckets that start inside a dword make the unpack's loads slower: 12 per CU there too (8B at 2^28 - 2:
-    // 4,838 us against 4,943 at 10; at 2^28 - 4: 4,792 against 4,797).
-    const size_t lds = occupancy_lds(0, kTileChunkBytes, (realign || B % 4 != 0 ? 48 : 40) << 10);
-    const bool through = ntm && 2 * s.total_bytes >= kThroughBucketBytes;
+    const size_t lds = occupancy_lds(0, rule.cap);
     const uint64_t recip = ~0ull / B;
     drop_pending_error();
     auto launch = [&](auto kernel) {
@@ -1184,8 +1137,8 @@ static int bucket_call(emu_plan_t plan, const void* ws, int32_t side, uint64_t B
     auto by_policy = [&](auto unpacks, auto realigns) {
       constexpr int U = kBucketTileVecs;
       constexpr bool kUnpack = decltype(unpacks)::value, kRealign = decltype(realigns)::value;
-      if (through) launch(k_buckets_tile<kUnpack, POL_THROUGH, U, kRealign>);
-      else if (ntm) launch(k_buckets_tile<kUnpack, POL_NT, U, kRealign>);
+      if (rule.policy == POL_THROUGH) launch(k_buckets_tile<kUnpack, POL_THROUGH, U, kRealign>);
+      else if (rule.policy == POL_NT) launch(k_buckets_tile<kUnpack, POL_NT, U, kRealign>);
       else launch(k_buckets_tile<kUnpack, POL_PLAIN, U, kRealign>);
     };
     if (unpack) realign ? by_policy(std::true_type(), std::true_type()) : by_policy(std::true_type(), std::false_type());
@@ -1207,9 +1160,9 @@ static int bucket_call(emu_plan_t plan, const void* ws, int32_t side, uint64_t B
 // `groups` tensor groups.
 static int launch_plan(const Plan* P, const uint8_t* w, const uint64_t* sp, const uint64_t* dp, uint32_t groups,
                        hipStream_t st, const char* what) {
-  const LaunchRule rule = launch_rule(P, groups);
+  const LaunchRule rule = reshard_rule(*P, groups);
   const ReshardLaunch l{reinterpret_cast<const DevSeg*>(w + P->ws.off_segs),
-                        reinterpret_cast<const uint32_t*>(w + P->ws.off_tilemap), P->ws.n_map, rule.flight,
+                        reinterpret_cast<const uint32_t*>(w + P->ws.off_tilemap), P->ws.n_map, rule.cap,
                         Tables{sp, dp, groups, uint32_t(P->side[0].tensors.size()), uint32_t(P->side[1].tensors.size())}, st};
   drop_pending_error();
   switch (P->tile_vecs) {

@@ -131,6 +131,18 @@ struct Plan {
   std::vector<uint8_t> host_ws;
 };
 
+// Cache policies of the kernels' loads and stores: plain, streaming, streaming and written through.
+enum Policy : int { POL_PLAIN = 0, POL_NT = 1, POL_THROUGH = 2 };
+
+// How one call is launched (emu_launch.cpp): the policy, and the most workgroups resident per CU (0: no cap).
+struct LaunchRule {
+  int policy;
+  int cap;
+};
+LaunchRule reshard_rule(const Plan& P, uint32_t groups);
+bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack);
+LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack);  // the tile-per-workgroup kernel
+
 uint64_t next_plan_id();
 
 // errors.cpp-style helpers (defined in emu_plan.cpp)

@@ -1,0 +1,66 @@
+// How one reshard, pack or unpack call is launched, from what it moves: the cache policy of its stores and
+// the most workgroups resident per CU. Host code of its own, so that the rules can be checked without a GPU.
+#include "emu.h"
+#include "emu_internal.h"
+
+namespace emu {
+
+// Residency bounds the bytes in flight per CU: on MI355X a copy stream runs fastest with about 24-48 KB in
+// flight per CU and drops by about 8% at 128 KB, where the HBM read/write mix degrades. Automatic (-1):
+// flight / tile_bytes workgroups, at least 2, and no cap from 32 up, with `flight` in destination bytes.
+static int resident(uint64_t tile_bytes, uint64_t flight) {
+  const int64_t set = option(EMU_OPT_WG_PER_CU);
+  if (set >= 0) return int(set);
+  const int64_t cap = int64_t(flight / (tile_bytes ? tile_bytes : 1));
+  return cap < 2 ? 2 : cap >= 32 ? 0 : int(cap);
+}
+
+// The reshard. Measured at 4 KB tiles, several settings in one process on the same buffers, with the states
+// in rotation that no cache holds:
+//  - Residency (flight, destination bytes in flight per CU). Copies: 48 KB; 8 / 10 / 12 / 14 tiles ran the 1B
+//    TP4 -> TP2 reshard in 912 / 890 / 890 / 900 us and a decoder with odd widths in 155 / 147 / 145 / 148.
+//    fp32 -> bf16, which reads twice what it writes: 24 KB; 4 / 6 / 8 / 10 tiles took 1548 / 1319 / 1340 / 1355 us
+//    on aligned 1B shards; with units at any alignment, whose address work is longer, 40 KB: 285 / 226 / 217 / 216
+//    on the odd widths. bf16 -> fp32, which reads half: written through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 /
+//    1372 us (1B, fused to separate formats), otherwise 48 KB, 10 / 12 / 14 / 16 tiles in 1414 / 1382 / 1394 / 1418.
+//  - Cache policy. Writing through gains from about 1 GB moved per launch on (1B copy 890 against 914 us, 8B 4823
+//    against 4928, fp32 -> bf16 1319 against 1335, bf16 -> fp32 1364 against 1382; copies with units at any alignment:
+//    odd widths, 4.8 GB, 724 against 743, 8B into and out of odd buckets 10.12 against 10.28 ms), not below (0.7 GB:
+//    107.2 against 105.5; 4 MB: 2.7 against 2.5), and not for conversions at any alignment (218 against 216, bf16 ->
+//    fp32 785 against 758).
+constexpr uint64_t kThroughBytes = 1ull << 30;  // read and written by one reshard launch
+
+LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
+  const bool any = P.info.n_general_segments > 0;
+  const uint64_t moved = (P.info.bytes_read + P.info.bytes_written) * groups;
+  int policy = POL_PLAIN;
+  if (option(EMU_OPT_NONTEMPORAL) != 0)
+    policy = moved >= kThroughBytes && (!any || P.cvt == CVT_NONE) ? POL_THROUGH : POL_NT;
+  uint64_t flight = 48 << 10;
+  if (P.cvt == CVT_F32_BF16) flight = (any ? 40 : 24) << 10;
+  else if (P.cvt == CVT_BF16_F32 && policy == POL_THROUGH) flight = 56 << 10;
+  return {policy, resident(P.tile_bytes, flight)};
+}
+
+// Pack and unpack cut chunks on the stream's grid unless the destination's differs: buckets whose size is not
+// a multiple of 4 KB (pack), tensors at stream offsets that are not (unpack).
+bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack) {
+  return unpack ? !s.offsets_grid : B % kTileChunkBytes != 0;
+}
+
+// Pack and unpack, residency and cache policy as for the reshard. 10 / 12 / 16 chunks per CU: 9,537 / 9,738 /
+// 10,087 us for the 8B pack and unpack, whose chunks end on tensor and bucket ends; 298 / 288 / 292 us where
+// chunks are moved to the destination's grid and hold several pieces (odd widths), and 168 / 162 / 165 in a set
+// of 0.26 GB. Writing through took 162 us there against 166 with "nt", 9,537 against 9,907 at 8B, and 100.5
+// against 99.7 at 0.15 GB. Buckets that start inside a dword make the unpack's loads slower: 12 per CU there
+// too (8B at 2^28 - 2: 4,838 us against 4,943 at 10; at 2^28 - 4: 4,792 against 4,797).
+constexpr uint64_t kThroughBucketBytes = 1ull << 29;  // read and written by one pack or unpack
+
+LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack) {
+  int policy = POL_PLAIN;
+  if (option(EMU_OPT_NONTEMPORAL) != 0) policy = 2 * s.total_bytes >= kThroughBucketBytes ? POL_THROUGH : POL_NT;
+  const bool shifted = chunks_realign(s, B, unpack) || B % 4 != 0;
+  return {policy, resident(kTileChunkBytes, (shifted ? 48 : 40) << 10)};
+}
+
+}  // namespace emu

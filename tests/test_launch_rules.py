@@ -1,0 +1,93 @@
+"""How calls are launched (stores' cache policy, workgroups resident per CU) on either side of each line of the
+rules, read through a probe linked to the built library. No GPU needed."""
+import contextlib
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2609_34645_amd import build, emu
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+PLAIN, NT, THROUGH = 0, 1, 2
+ONE_B = (16, 2048, 32, 64, 8, 8192, 128256)
+RAGGED = (12, 996, 12, 83, 6, 2658, 50257)
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ is not available")
+    if not os.path.exists(emu.LIB_PATH):
+        build.build()
+    emu.load()
+    so = str(tmp_path_factory.mktemp("probe") / "probe.so")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+                    os.path.join(HERE, "launch_rules_probe.cpp"), emu.LIB_PATH, f"-Wl,-rpath,{build.PKG}", "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    lib.probe_reshard.argtypes = [ctypes.c_void_p, ctypes.c_uint32, ctypes.c_void_p]
+    lib.probe_bucket.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint64, ctypes.c_int32, ctypes.c_void_p]
+    lib.probe_reshard.restype = lib.probe_bucket.restype = None
+    return lib
+
+
+@contextlib.contextmanager
+def options(**kw):
+    keys = {getattr(emu, "OPT_" + k): v for k, v in kw.items()}
+    old = {k: emu.get_option(k) for k in keys}
+    try:
+        for k, v in keys.items():
+            emu.set_option(k, v)
+        yield
+    finally:
+        for k, v in old.items():
+            emu.set_option(k, v)
+
+
+def plan(shape, src, dst, sdt="bf16", ddt="bf16", pads=(0, 0), **kw):
+    m = emu.Model(*shape)
+    return emu.Plan(emu.Layout(m, *src, pads[0], sdt), emu.Layout(m, *dst, pads[1], ddt), **kw)
+
+
+def reshard(probe, p, groups=1):
+    out = (ctypes.c_int32 * 2)()
+    probe.probe_reshard(p._h, groups, out)
+    return tuple(out)
+
+
+def bucket(probe, p, B, unpack, side=0):
+    out = (ctypes.c_int32 * 2)()
+    probe.probe_bucket(p._h, side, B, int(unpack), out)
+    return tuple(out)
+
+
+def test_reshard_by_bytes_moved(probe):
+    """Large transfers write through, small ones do not, and the groups of one launch count together."""
+    big, small = plan(ONE_B, (4, 1), (2, 1)), plan((2, 256, 4, 64, 2, 688, 1024), (1, 1), (2, 1))
+    assert reshard(probe, big) == (THROUGH, 12) and reshard(probe, small) == (NT, 12)
+    moved = small.info["bytes_read"] + small.info["bytes_written"]
+    n = -(-(1 << 30) // moved)
+    assert reshard(probe, small, n - 1) == (NT, 12) and reshard(probe, small, n) == (THROUGH, 12)
+    with options(NONTEMPORAL=0):
+        assert reshard(probe, big) == (PLAIN, 12)
+    with options(WG_PER_CU=7):
+        assert reshard(probe, big) == (THROUGH, 7)
+
+
+def test_reshard_conversions(probe):
+    assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "fp32", "bf16")) == (THROUGH, 6)
+    assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32")) == (THROUGH, 14)
+    assert reshard(probe, plan(RAGGED, (2, 1), (1, 2), "bf16", "fp32", (64, 64))) == (NT, 12)  # mostly misaligned
+
+
+def test_buckets_by_set_size(probe):
+    big = plan(ONE_B, (4, 1), (4, 1))
+    for unpack in (False, True):
+        assert bucket(probe, big, 1 << 28, unpack) == (THROUGH, 10)
+        assert bucket(probe, big, (1 << 28) - 2, unpack) == (THROUGH, 12)
+        with options(NONTEMPORAL=0):
+            assert bucket(probe, big, 1 << 28, unpack) == (PLAIN, 10)
+    small = plan((2, 256, 4, 64, 2, 688, 1024), (2, 1), (2, 1))
+    assert bucket(probe, small, 1 << 16, False)[0] == NT
