@@ -20,24 +20,26 @@ static int resident(uint64_t tile_bytes, uint64_t flight) {
 //  - Residency (flight, destination bytes in flight per CU). Copies: 48 KB; 8 / 10 / 12 / 14 tiles ran the 1B
 //    TP4 -> TP2 reshard in 912 / 890 / 890 / 900 us and a decoder with odd widths in 155 / 147 / 145 / 148.
 //    fp32 -> bf16, which reads twice what it writes: 24 KB; 4 / 6 / 8 / 10 tiles took 1548 / 1319 / 1340 / 1355 us
-//    on aligned 1B shards; with units at any alignment, whose address work is longer, 40 KB: 285 / 226 / 217 / 216
-//    on the odd widths. bf16 -> fp32, which reads half: written through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 /
-//    1372 us (1B, fused to separate formats), otherwise 48 KB, 10 / 12 / 14 / 16 tiles in 1414 / 1382 / 1394 / 1418.
+//    on aligned 1B shards, and with units at any alignment 248 / 211 / 213 / 214 (odd widths, 1.4 GB) and 2377 /
+//    2072 / 2108 / 2115 (8 layers of the 8B decoder into odd buckets). bf16 -> fp32, which reads half: written
+//    through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 / 1372 us (1B, fused to separate formats), otherwise 48 KB,
+//    10 / 12 / 14 / 16 tiles in 1414 / 1382 / 1394 / 1418.
 //  - Cache policy. Writing through gains from about 1 GB moved per launch on (1B copy 890 against 914 us, 8B 4823
 //    against 4928, fp32 -> bf16 1319 against 1335, bf16 -> fp32 1364 against 1382; copies with units at any alignment:
 //    odd widths, 4.8 GB, 724 against 743, 8B into and out of odd buckets 10.12 against 10.28 ms), not below (0.7 GB:
-//    107.2 against 105.5; 4 MB: 2.7 against 2.5), and not for conversions at any alignment (218 against 216, bf16 ->
-//    fp32 785 against 758).
+//    107.2 against 105.5; 4 MB: 2.7 against 2.5). Conversions: by the share of their bytes at any alignment, with
+//    the line at an eighth. Written through / streaming, fp32 -> bf16 at a share of 0 / 0.006 / 0.22 / 0.67 / 0.8:
+//    1070 / 1079, 992 / 1002, 1089 / 1088, 1113 / 1096 and 447 / 443 us; bf16 -> fp32 at 0 / 0.006 / 0.22 / 0.67:
+//    1104 / 1108, 1017 / 1028, 1119 / 1116 and 1133 / 1127.
 constexpr uint64_t kThroughBytes = 1ull << 30;  // read and written by one reshard launch
 
 LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
-  const bool any = P.info.n_general_segments > 0;
   const uint64_t moved = (P.info.bytes_read + P.info.bytes_written) * groups;
+  const bool whole = P.cvt == CVT_NONE || P.any_bytes < P.info.bytes_written / 8;
   int policy = POL_PLAIN;
-  if (option(EMU_OPT_NONTEMPORAL) != 0)
-    policy = moved >= kThroughBytes && (!any || P.cvt == CVT_NONE) ? POL_THROUGH : POL_NT;
+  if (option(EMU_OPT_NONTEMPORAL) != 0) policy = moved >= kThroughBytes && whole ? POL_THROUGH : POL_NT;
   uint64_t flight = 48 << 10;
-  if (P.cvt == CVT_F32_BF16) flight = (any ? 40 : 24) << 10;
+  if (P.cvt == CVT_F32_BF16) flight = 24 << 10;
   else if (P.cvt == CVT_BF16_F32 && policy == POL_THROUGH) flight = 56 << 10;
   return {policy, resident(P.tile_bytes, flight)};
 }

@@ -594,6 +594,7 @@ static int finalize(Plan& P) {
   const uint64_t salign = P.cvt == CVT_BF16_F32 ? 8 : 16;
   const uint64_t esd = uint64_t(elem_size(P.side[1].lay.dtype));
   int32_t ngeneral = 0;
+  P.any_bytes = 0;
   const bool row_wrap = option(EMU_OPT_ROW_WRAP) != 0;
   for (size_t i = 0; i < P.segs.size(); ++i) {
     const emu_segment_t& g = P.segs[i];
@@ -634,6 +635,7 @@ static int finalize(Plan& P) {
         nt = g.rows * tpr;
       }
       ++ngeneral;
+      if (!zero) P.any_bytes += g.rows * g.run;
     } else if (g.rows == 1) {
       d.mode = SEG_VEC_1D;
       nt = (g.run + TB - 1) / TB;

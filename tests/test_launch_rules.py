@@ -76,10 +76,20 @@ def test_reshard_by_bytes_moved(probe):
         assert reshard(probe, big) == (THROUGH, 7)
 
 
-def test_reshard_conversions(probe):
-    assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "fp32", "bf16")) == (THROUGH, 6)
-    assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32")) == (THROUGH, 14)
-    assert reshard(probe, plan(RAGGED, (2, 1), (1, 2), "bf16", "fp32", (64, 64))) == (NT, 12)  # mostly misaligned
+@pytest.mark.parametrize("pair, few, many", [(("fp32", "bf16"), (THROUGH, 6), (NT, 6)),
+                                             (("bf16", "fp32"), (THROUGH, 14), (NT, 12))], ids=["narrow", "widen"])
+def test_conversions_by_share_of_misaligned_bytes(probe, pair, few, many):
+    """One misaligned segment does not change how the rest of a large converting plan is launched: the share of
+    misaligned bytes decides, from an eighth on. Zero fill has no share, aligned or not."""
+    assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), *pair)) == few
+    # o's slices of 66 columns per rank: 0.6% of the bytes
+    p = plan((6, 4096, 4, 66, 4, 11008, 32000), (4, 1), (2, 1), *pair)
+    assert p.info["n_general_segments"] > 0 and reshard(probe, p) == few
+    # tensors of odd sizes, and zero fill that starts between vectors: 5%
+    p = plan((6, 4098, 32, 64, 8, 11008, 32001), (4, 1), (4, 1), *pair, (8, 16))
+    assert p.info["n_general_segments"] > 0 and p.info["zero_fill_bytes"] > 0 and reshard(probe, p) == few
+    assert reshard(probe, plan((6, 4096, 32, 64, 8, 11004, 32000), (4, 1), (2, 1), *pair)) == many  # down: 22%
+    assert reshard(probe, plan(RAGGED, (2, 1), (1, 2), *pair, (64, 64))) == many
 
 
 def test_buckets_by_set_size(probe):
