@@ -7,12 +7,12 @@ namespace emu {
 
 // Residency bounds the bytes in flight per CU: on MI355X a copy stream runs fastest with about 24-48 KB in
 // flight per CU and drops by about 8% at 128 KB, where the HBM read/write mix degrades. Automatic (-1):
-// flight / tile_bytes workgroups, at least 2, and no cap from 32 up, with `flight` in destination bytes.
-static int resident(uint64_t tile_bytes, uint64_t flight) {
+// flight / tile_bytes workgroups, at least `least`, and no cap from 32 up, with `flight` in destination bytes.
+static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
   const int64_t set = option(EMU_OPT_WG_PER_CU);
   if (set >= 0) return int(set);
   const int64_t cap = int64_t(flight / (tile_bytes ? tile_bytes : 1));
-  return cap < 2 ? 2 : cap >= 32 ? 0 : int(cap);
+  return cap < least ? least : cap >= 32 ? 0 : int(cap);
 }
 
 // The reshard. Measured at 4 KB tiles, several settings in one process on the same buffers, with the states
@@ -23,7 +23,9 @@ static int resident(uint64_t tile_bytes, uint64_t flight) {
 //    on aligned 1B shards, and with units at any alignment 248 / 211 / 213 / 214 (odd widths, 1.4 GB) and 2377 /
 //    2072 / 2108 / 2115 (8 layers of the 8B decoder into odd buckets). bf16 -> fp32, which reads half: written
 //    through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 / 1372 us (1B, fused to separate formats), otherwise 48 KB,
-//    10 / 12 / 14 / 16 tiles in 1414 / 1382 / 1394 / 1418.
+//    10 / 12 / 14 / 16 tiles in 1414 / 1382 / 1394 / 1418. Conversions keep at least 4 of the larger tiles: 2 / 4 / 6
+//    took 1895 / 1378 / 1447 us at 8 KB (fp32 -> bf16), 1776 / 1473 / 1527 at 16 KB, and 1637 / 1391 / 1447 for
+//    bf16 -> fp32 at 16 KB. Copies at 16 KB run best with 2: 929 / 974 / 1009.
 //  - Cache policy. Writing through gains from about 1 GB moved per launch on (1B copy 890 against 914 us, 8B 4823
 //    against 4928, fp32 -> bf16 1319 against 1335, bf16 -> fp32 1364 against 1382; copies with units at any alignment:
 //    odd widths, 4.8 GB, 724 against 743, 8B into and out of odd buckets 10.12 against 10.28 ms), not below (0.7 GB:
@@ -41,7 +43,7 @@ LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
   uint64_t flight = 48 << 10;
   if (P.cvt == CVT_F32_BF16) flight = 24 << 10;
   else if (P.cvt == CVT_BF16_F32 && policy == POL_THROUGH) flight = 56 << 10;
-  return {policy, resident(P.tile_bytes, flight)};
+  return {policy, resident(P.tile_bytes, flight, P.cvt == CVT_NONE ? 2 : 4)};
 }
 
 // Pack and unpack cut chunks on the stream's grid unless the destination's differs: buckets whose size is not

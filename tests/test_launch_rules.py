@@ -92,6 +92,15 @@ def test_conversions_by_share_of_misaligned_bytes(probe, pair, few, many):
     assert reshard(probe, plan(RAGGED, (2, 1), (1, 2), *pair, (64, 64))) == many
 
 
+@pytest.mark.parametrize("tile_vecs, copy, narrow, widen", [(1, 0, 24, 0), (2, 24, 12, 28), (8, 6, 4, 7), (16, 3, 4, 4)])
+def test_residency_at_other_tile_sizes(probe, tile_vecs, copy, narrow, widen):
+    """The bytes in flight that 4 KB tiles run best with, but not fewer than 4 of the larger tiles in conversions."""
+    with options(TILE_VECS=tile_vecs):
+        assert reshard(probe, plan(ONE_B, (4, 1), (2, 1)))[1] == copy
+        assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "fp32", "bf16"))[1] == narrow
+        assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32"))[1] == widen
+
+
 def test_buckets_by_set_size(probe):
     big = plan(ONE_B, (4, 1), (4, 1))
     for unpack in (False, True):
