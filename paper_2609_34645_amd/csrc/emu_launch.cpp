@@ -32,18 +32,19 @@ static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
 //    107.2 against 105.5; 4 MB: 2.7 against 2.5). Conversions: by the share of their bytes at any alignment, with
 //    the line at an eighth. Written through / streaming, fp32 -> bf16 at a share of 0 / 0.006 / 0.22 / 0.67 / 0.8:
 //    1070 / 1079, 992 / 1002, 1089 / 1088, 1113 / 1096 and 447 / 443 us; bf16 -> fp32 at 0 / 0.006 / 0.22 / 0.67:
-//    1104 / 1108, 1017 / 1028, 1119 / 1116 and 1133 / 1127.
+//    1104 / 1108, 1017 / 1028, 1119 / 1116 and 1133 / 1127. Without a cap on the residency, written-through stores
+//    congest sooner than streaming ones: bf16 -> fp32 at 1 KB tiles 1636 against 1573 us, at 4 KB 1522 against 1450.
 constexpr uint64_t kThroughBytes = 1ull << 30;  // read and written by one reshard launch
 
 LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
   const uint64_t moved = (P.info.bytes_read + P.info.bytes_written) * groups;
   const bool whole = P.cvt == CVT_NONE || P.any_bytes < P.info.bytes_written / 8;
-  int policy = POL_PLAIN;
-  if (option(EMU_OPT_NONTEMPORAL) != 0) policy = moved >= kThroughBytes && whole ? POL_THROUGH : POL_NT;
-  uint64_t flight = 48 << 10;
-  if (P.cvt == CVT_F32_BF16) flight = 24 << 10;
-  else if (P.cvt == CVT_BF16_F32 && policy == POL_THROUGH) flight = 56 << 10;
-  return {policy, resident(P.tile_bytes, flight, P.cvt == CVT_NONE ? 2 : 4)};
+  const int least = P.cvt == CVT_NONE ? 2 : 4;
+  const auto cap = [&](uint64_t kb) { return resident(P.tile_bytes, kb << 10, least); };
+  const LaunchRule stream{POL_NT, cap(P.cvt == CVT_F32_BF16 ? 24 : 48)};
+  if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, stream.cap};
+  const LaunchRule through{POL_THROUGH, cap(P.cvt == CVT_F32_BF16 ? 24 : P.cvt == CVT_BF16_F32 ? 56 : 48)};
+  return moved >= kThroughBytes && whole && through.cap != 0 ? through : stream;
 }
 
 // Pack and unpack cut chunks on the stream's grid unless the destination's differs: buckets whose size is not
@@ -57,14 +58,15 @@ bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack) {
 // chunks are moved to the destination's grid and hold several pieces (odd widths), and 168 / 162 / 165 in a set
 // of 0.26 GB. Writing through took 162 us there against 166 with "nt", 9,537 against 9,907 at 8B, and 100.5
 // against 99.7 at 0.15 GB. Buckets that start inside a dword make the unpack's loads slower: 12 per CU there
-// too (8B at 2^28 - 2: 4,838 us against 4,943 at 10; at 2^28 - 4: 4,792 against 4,797).
+// too (8B at 2^28 - 2: 4,838 us against 4,943 at 10; at 2^28 - 4: 4,792 against 4,797). Without a cap on the
+// residency, writing through loses: 8B pack 5,339 us against 5,036, unpack 5,383 against 5,020.
 constexpr uint64_t kThroughBucketBytes = 1ull << 29;  // read and written by one pack or unpack
 
 LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack) {
-  int policy = POL_PLAIN;
-  if (option(EMU_OPT_NONTEMPORAL) != 0) policy = 2 * s.total_bytes >= kThroughBucketBytes ? POL_THROUGH : POL_NT;
   const bool shifted = chunks_realign(s, B, unpack) || B % 4 != 0;
-  return {policy, resident(kTileChunkBytes, (shifted ? 48 : 40) << 10)};
+  const int cap = resident(kTileChunkBytes, (shifted ? 48 : 40) << 10);
+  if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, cap};
+  return {2 * s.total_bytes >= kThroughBucketBytes && cap != 0 ? POL_THROUGH : POL_NT, cap};
 }
 
 }  // namespace emu
