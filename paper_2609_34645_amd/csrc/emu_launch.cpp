@@ -22,8 +22,8 @@ static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
 //    fp32 -> bf16, which reads twice what it writes: 24 KB; 4 / 6 / 8 / 10 tiles took 1548 / 1319 / 1340 / 1355 us
 //    on aligned 1B shards, and with units at any alignment 248 / 211 / 213 / 214 (odd widths, 1.4 GB) and 2377 /
 //    2072 / 2108 / 2115 (8 layers of the 8B decoder into odd buckets). bf16 -> fp32, which reads half: written
-//    through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 / 1372 us (1B, fused to separate formats), otherwise 48 KB,
-//    10 / 12 / 14 / 16 tiles in 1414 / 1382 / 1394 / 1418. Conversions keep at least 4 of the larger tiles: 2 / 4 / 6
+//    through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 / 1372 us (1B, fused to separate formats), with plain stores
+//    56 KB, 10 / 12 / 14 / 16 in 1623 / 1498 / 1459 / 1461, streaming 48 KB, in 1414 / 1382 / 1394 / 1418. Conversions keep at least 4 of the larger tiles: 2 / 4 / 6
 //    took 1895 / 1378 / 1447 us at 8 KB (fp32 -> bf16), 1776 / 1473 / 1527 at 16 KB, and 1637 / 1391 / 1447 for
 //    bf16 -> fp32 at 16 KB. Copies at 16 KB run best with 2: 929 / 974 / 1009.
 //  - Cache policy. Writing through gains from about 1 GB moved per launch on (1B copy 890 against 914 us, 8B 4823
@@ -42,8 +42,8 @@ LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
   const int least = P.cvt == CVT_NONE ? 2 : 4;
   const auto cap = [&](uint64_t kb) { return resident(P.tile_bytes, kb << 10, least); };
   const LaunchRule stream{POL_NT, cap(P.cvt == CVT_F32_BF16 ? 24 : 48)};
-  if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, stream.cap};
   const LaunchRule through{POL_THROUGH, cap(P.cvt == CVT_F32_BF16 ? 24 : P.cvt == CVT_BF16_F32 ? 56 : 48)};
+  if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, through.cap};
   return moved >= kThroughBytes && whole && through.cap != 0 ? through : stream;
 }
 

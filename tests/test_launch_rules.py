@@ -72,6 +72,8 @@ def test_reshard_by_bytes_moved(probe):
     assert reshard(probe, small, n - 1) == (NT, 12) and reshard(probe, small, n) == (THROUGH, 12)
     with options(NONTEMPORAL=0):
         assert reshard(probe, big) == (PLAIN, 12)
+        assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "fp32", "bf16")) == (PLAIN, 6)
+        assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32")) == (PLAIN, 14)
     with options(WG_PER_CU=7):
         assert reshard(probe, big) == (THROUGH, 7)
 
