@@ -23,9 +23,10 @@ static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
 //    on aligned 1B shards, and with units at any alignment 248 / 211 / 213 / 214 (odd widths, 1.4 GB) and 2377 /
 //    2072 / 2108 / 2115 (8 layers of the 8B decoder into odd buckets). bf16 -> fp32, which reads half: written
 //    through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 / 1372 us (1B, fused to separate formats), with plain stores
-//    56 KB, 10 / 12 / 14 / 16 in 1623 / 1498 / 1459 / 1461, streaming 48 KB, in 1414 / 1382 / 1394 / 1418. Conversions keep at least 4 of the larger tiles: 2 / 4 / 6
-//    took 1895 / 1378 / 1447 us at 8 KB (fp32 -> bf16), 1776 / 1473 / 1527 at 16 KB, and 1637 / 1391 / 1447 for
-//    bf16 -> fp32 at 16 KB. Copies at 16 KB run best with 2: 929 / 974 / 1009.
+//    56 KB, 10 / 12 / 14 / 16 in 1623 / 1498 / 1459 / 1461, streaming 48 KB, in 1414 / 1382 / 1394 / 1418.
+//    Conversions keep at least 4 of the larger tiles: 2 / 4 / 6 took 1895 / 1378 / 1447 us at 8 KB (fp32 -> bf16),
+//    1776 / 1473 / 1527 at 16 KB, and 1637 / 1391 / 1447 for bf16 -> fp32 at 16 KB. Copies at 16 KB run best with
+//    2: 929 / 974 / 1009.
 //  - Cache policy. Writing through gains from about 1 GB moved per launch on (1B copy 890 against 914 us, 8B 4823
 //    against 4928, fp32 -> bf16 1319 against 1335, bf16 -> fp32 1364 against 1382; copies with units at any alignment:
 //    odd widths, 4.8 GB, 724 against 743, 8B into and out of odd buckets 10.12 against 10.28 ms), not below (0.7 GB:
@@ -58,12 +59,13 @@ bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack) {
 // chunks are moved to the destination's grid and hold several pieces (odd widths), and 168 / 162 / 165 in a set
 // of 0.26 GB. Writing through took 162 us there against 166 with "nt", 9,537 against 9,907 at 8B, and 100.5
 // against 99.7 at 0.15 GB. Buckets that start inside a dword make the unpack's loads slower: 12 per CU there
-// too (8B at 2^28 - 2: 4,838 us against 4,943 at 10; at 2^28 - 4: 4,792 against 4,797). Without a cap on the
+// too (8B at 2^28 - 2: 4,838 us against 4,943 at 10; at 2^28 - 4: 4,792 against 4,797), and tensors off the 4 KB
+// grid the pack's, whatever the buckets (odd widths in 4 MB buckets, 2.3 GB: 708 us against 722). Without a cap on the
 // residency, writing through loses: 8B pack 5,339 us against 5,036, unpack 5,383 against 5,020.
 constexpr uint64_t kThroughBucketBytes = 1ull << 29;  // read and written by one pack or unpack
 
 LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack) {
-  const bool shifted = chunks_realign(s, B, unpack) || B % 4 != 0;
+  const bool shifted = !s.offsets_grid || chunks_realign(s, B, unpack) || B % 4 != 0;
   const int cap = resident(kTileChunkBytes, (shifted ? 48 : 40) << 10);
   if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, cap};
   return {2 * s.total_bytes >= kThroughBucketBytes && cap != 0 ? POL_THROUGH : POL_NT, cap};

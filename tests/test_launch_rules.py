@@ -112,6 +112,12 @@ def test_no_write_through_without_a_cap(probe):
         assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32")) == (NT, 0)
 
 
+def test_tensors_off_the_grid(probe):
+    """Buckets on the 4 KB grid, tensors off it: the pack reads at any phase, the unpack moves its chunks."""
+    p = plan((10, 1997, 12, 66, 12, 7896, 6653), (3, 3), (3, 3), pads=(8, 8))
+    assert bucket(probe, p, 1 << 22, False)[1] == bucket(probe, p, 1 << 22, True)[1] == 12
+
+
 def test_buckets_by_set_size(probe):
     big = plan(ONE_B, (4, 1), (4, 1))
     for unpack in (False, True):
