@@ -56,19 +56,26 @@ bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack) {
 
 // Pack and unpack, residency and cache policy as for the reshard. 10 / 12 / 16 chunks per CU: 9,537 / 9,738 /
 // 10,087 us for the 8B pack and unpack, whose chunks end on tensor and bucket ends; 298 / 288 / 292 us where
-// chunks are moved to the destination's grid and hold several pieces (odd widths), and 168 / 162 / 165 in a set
-// of 0.26 GB. Writing through took 162 us there against 166 with "nt", 9,537 against 9,907 at 8B, and 100.5
-// against 99.7 at 0.15 GB. Buckets that start inside a dword make the unpack's loads slower: 12 per CU there
-// too (8B at 2^28 - 2: 4,838 us against 4,943 at 10; at 2^28 - 4: 4,792 against 4,797), and tensors off the 4 KB
-// grid the pack's, whatever the buckets (odd widths in 4 MB buckets, 2.3 GB: 708 us against 722). Without a cap on the
-// residency, writing through loses: 8B pack 5,339 us against 5,036, unpack 5,383 against 5,020.
-constexpr uint64_t kThroughBucketBytes = 1ull << 29;  // read and written by one pack or unpack
+// chunks are moved to the destination's grid and hold several pieces (odd widths). Buckets that start inside a
+// dword make the unpack's loads slower: 12 per CU there too (8B at 2^28 - 2: 4,838 us against 4,943 at 10; at
+// 2^28 - 4: 4,792 against 4,797), and tensors off the 4 KB grid the pack's, whatever the buckets (odd widths in
+// 4 MB buckets, 2.3 GB: 708 us against 722). Without a cap on the residency, writing through loses: 8B pack 5,339
+// us against 5,036, unpack 5,383 against 5,020.
+//
+// Written through / streaming, with sets in rotation that no cache holds. Buckets on the 4 KB grid, unpack 10.97 /
+// 10.84 us (a set of 26 MB), 17.6 / 18.3 (49 MB), 25.2 / 25.8 (75), 40.1 / 41.6 (128), 95.3 / 98.8 (317), 901 / 936
+// (3.0 GB, pack 900 / 941), with odd widths 25.6 / 26.1 (76 MB), 64.1 / 65.8 (207). Other bucket sizes, where pieces
+// stored under lane masks lose what the others gain, unpack 25.9 / 25.9 (76 MB), 39.0 / 39.0 (120), 65.3 / 65.2 (207,
+// pack 65.9 / 65.6), 91.7 / 91.9 (295, pack 92.2 / 92.3), 174 / 176 (557).
+constexpr uint64_t kThroughGrid = 1ull << 27;   // read and written by one pack or unpack, buckets on the grid
+constexpr uint64_t kThroughOther = 1ull << 29;  // other bucket sizes
 
 LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack) {
   const bool shifted = !s.offsets_grid || chunks_realign(s, B, unpack) || B % 4 != 0;
   const int cap = resident(kTileChunkBytes, (shifted ? 48 : 40) << 10);
   if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, cap};
-  return {2 * s.total_bytes >= kThroughBucketBytes && cap != 0 ? POL_THROUGH : POL_NT, cap};
+  const uint64_t from = B % kTileChunkBytes == 0 ? kThroughGrid : kThroughOther;
+  return {2 * s.total_bytes >= from && cap != 0 ? POL_THROUGH : POL_NT, cap};
 }
 
 }  // namespace emu

@@ -125,5 +125,15 @@ def test_buckets_by_set_size(probe):
         assert bucket(probe, big, (1 << 28) - 2, unpack) == (THROUGH, 12)
         with options(NONTEMPORAL=0):
             assert bucket(probe, big, 1 << 28, unpack) == (PLAIN, 10)
-    small = plan((2, 256, 4, 64, 2, 688, 1024), (2, 1), (2, 1))
-    assert bucket(probe, small, 1 << 16, False)[0] == NT
+    # sets of 49 and 128 MB: buckets on the 4 KB grid write through from 67 MB on, others from 268 MB
+    for shape, policy in (((2, 512, 8, 64, 4, 2048, 16384), NT), ((4, 1024, 16, 64, 8, 2816, 8192), THROUGH)):
+        p = plan(shape, (2, 1), (2, 1))
+        for unpack in (False, True):
+            assert bucket(probe, p, 1 << 24, unpack) == (policy, 12)
+            assert bucket(probe, p, (1 << 24) - 2, unpack) == (NT, 12)
+    for layers, policy in ((3, NT), (4, THROUGH)):
+        p = plan((layers, 996, 12, 83, 6, 2658, 50257), (2, 1), (2, 1), pads=(64, 64))
+        assert (p.info["src_bytes"] >= 1 << 28) == (policy == THROUGH)
+        for unpack in (False, True):
+            assert bucket(probe, p, 1 << 22, unpack) == (THROUGH, 12)
+            assert bucket(probe, p, (1 << 22) + 2, unpack) == (policy, 12)
