@@ -33,8 +33,9 @@ static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
 //    107.2 against 105.5; 4 MB: 2.7 against 2.5). Conversions: by the share of their bytes at any alignment, with
 //    the line at an eighth. Written through / streaming, fp32 -> bf16 at a share of 0 / 0.006 / 0.22 / 0.67 / 0.8:
 //    1070 / 1079, 992 / 1002, 1089 / 1088, 1113 / 1096 and 447 / 443 us; bf16 -> fp32 at 0 / 0.006 / 0.22 / 0.67:
-//    1104 / 1108, 1017 / 1028, 1119 / 1116 and 1133 / 1127. Without a cap on the residency, written-through stores
-//    congest sooner than streaming ones: bf16 -> fp32 at 1 KB tiles 1636 against 1573 us, at 4 KB 1522 against 1450.
+//    1104 / 1108, 1017 / 1028, 1119 / 1116 and 1133 / 1127. Widening at 1 KB tiles, whose
+//    residency has no cap, streams: 1601 us against 1635 (without a cap at 4 KB, 1559 against 1518: the option alone
+//    does not decide it).
 constexpr uint64_t kThroughBytes = 1ull << 30;  // read and written by one reshard launch
 
 LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
@@ -45,7 +46,8 @@ LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
   const LaunchRule stream{POL_NT, cap(P.cvt == CVT_F32_BF16 ? 24 : 48)};
   const LaunchRule through{POL_THROUGH, cap(P.cvt == CVT_F32_BF16 ? 24 : P.cvt == CVT_BF16_F32 ? 56 : 48)};
   if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, through.cap};
-  return moved >= kThroughBytes && whole && through.cap != 0 ? through : stream;
+  const bool thin = P.cvt == CVT_BF16_F32 && P.tile_vecs == 1;
+  return moved >= kThroughBytes && whole && !thin ? through : stream;
 }
 
 // Pack and unpack cut chunks on the stream's grid unless the destination's differs: buckets whose size is not
@@ -59,8 +61,7 @@ bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack) {
 // chunks are moved to the destination's grid and hold several pieces (odd widths). Buckets that start inside a
 // dword make the unpack's loads slower: 12 per CU there too (8B at 2^28 - 2: 4,838 us against 4,943 at 10; at
 // 2^28 - 4: 4,792 against 4,797), and tensors off the 4 KB grid the pack's, whatever the buckets (odd widths in
-// 4 MB buckets, 2.3 GB: 708 us against 722). Without a cap on the residency, writing through loses: 8B pack 5,339
-// us against 5,036, unpack 5,383 against 5,020.
+// 4 MB buckets, 2.3 GB: 708 us against 722).
 //
 // Written through / streaming, with sets in rotation that no cache holds. Buckets on the 4 KB grid, unpack 10.97 /
 // 10.84 us (a set of 26 MB), 17.6 / 18.3 (49 MB), 25.2 / 25.8 (75), 40.1 / 41.6 (128), 95.3 / 98.8 (317), 901 / 936
@@ -75,7 +76,7 @@ LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack) {
   const int cap = resident(kTileChunkBytes, (shifted ? 48 : 40) << 10);
   if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, cap};
   const uint64_t from = B % kTileChunkBytes == 0 ? kThroughGrid : kThroughOther;
-  return {2 * s.total_bytes >= from && cap != 0 ? POL_THROUGH : POL_NT, cap};
+  return {2 * s.total_bytes >= from ? POL_THROUGH : POL_NT, cap};
 }
 
 }  // namespace emu

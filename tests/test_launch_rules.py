@@ -103,12 +103,13 @@ def test_residency_at_other_tile_sizes(probe, tile_vecs, copy, narrow, widen):
         assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32"))[1] == widen
 
 
-def test_no_write_through_without_a_cap(probe):
+def test_write_through_without_a_cap(probe):
     big, wide = plan(ONE_B, (4, 1), (2, 1)), plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32")
     with options(WG_PER_CU=0):
-        assert reshard(probe, big) == reshard(probe, wide) == (NT, 0)
-        assert bucket(probe, big, 1 << 28, False) == bucket(probe, big, 1 << 28, True) == (NT, 0)
+        assert reshard(probe, big) == reshard(probe, wide) == (THROUGH, 0)
+        assert bucket(probe, big, 1 << 28, False) == bucket(probe, big, 1 << 28, True) == (THROUGH, 0)
     with options(TILE_VECS=1):
+        assert reshard(probe, plan(ONE_B, (4, 1), (2, 1))) == (THROUGH, 0)
         assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32")) == (NT, 0)
 
 
