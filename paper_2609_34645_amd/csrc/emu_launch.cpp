@@ -65,10 +65,11 @@ bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack) {
 //
 // Written through / streaming, with sets in rotation that no cache holds. Buckets on the 4 KB grid, unpack 10.97 /
 // 10.84 us (a set of 26 MB), 17.6 / 18.3 (49 MB), 25.2 / 25.8 (75), 40.1 / 41.6 (128), 95.3 / 98.8 (317), 901 / 936
-// (3.0 GB, pack 900 / 941), with odd widths 25.6 / 26.1 (76 MB), 64.1 / 65.8 (207). Other bucket sizes, where pieces
-// stored under lane masks lose what the others gain, unpack 25.9 / 25.9 (76 MB), 39.0 / 39.0 (120), 65.3 / 65.2 (207,
-// pack 65.9 / 65.6), 91.7 / 91.9 (295, pack 92.2 / 92.3), 174 / 176 (557).
-constexpr uint64_t kThroughGrid = 1ull << 27;   // read and written by one pack or unpack, buckets on the grid
+// (3.0 GB, pack 900 / 941), with odd widths 25.6 / 26.1 (76 MB), 64.1 / 65.8 (207). A set and its buckets that fit
+// the last-level cache (256 MB) and are moved again stream better: pack 40.9 / 40.3 (125 MB), so the line lies there.
+// Other bucket sizes, where pieces stored under lane masks lose what the others gain, unpack 25.9 / 25.9 (76 MB),
+// 39.0 / 39.0 (120), 65.3 / 65.2 (207, pack 65.9 / 65.6), 91.7 / 91.9 (295, pack 92.2 / 92.3), 174 / 176 (557).
+constexpr uint64_t kThroughGrid = 1ull << 28;   // read and written by one pack or unpack, buckets on the grid
 constexpr uint64_t kThroughOther = 1ull << 29;  // other bucket sizes
 
 LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack) {

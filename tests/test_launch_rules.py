@@ -126,8 +126,8 @@ def test_buckets_by_set_size(probe):
         assert bucket(probe, big, (1 << 28) - 2, unpack) == (THROUGH, 12)
         with options(NONTEMPORAL=0):
             assert bucket(probe, big, 1 << 28, unpack) == (PLAIN, 10)
-    # sets of 49 and 128 MB: buckets on the 4 KB grid write through from 67 MB on, others from 268 MB
-    for shape, policy in (((2, 512, 8, 64, 4, 2048, 16384), NT), ((4, 1024, 16, 64, 8, 2816, 8192), THROUGH)):
+    # sets of 128 and 152 MB: buckets on the 4 KB grid write through from 134 MB on, others from 268 MB
+    for shape, policy in (((4, 1024, 16, 64, 8, 2816, 8192), NT), ((5, 1024, 16, 64, 8, 2816, 8192), THROUGH)):
         p = plan(shape, (2, 1), (2, 1))
         for unpack in (False, True):
             assert bucket(probe, p, 1 << 24, unpack) == (policy, 12)
