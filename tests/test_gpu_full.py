@@ -1,6 +1,7 @@
 """GPU parity at full benchmark sizes, in the launch configuration the benchmark times.
 
 * 1B-class decoder, TP4 PP1 -> TP2 PP1 (bf16): every byte against the oracle.
+* A decoder with odd widths (1.2 GB moved): reshard, pack and unpack written through, every byte against the oracle.
 * 8B decoder, TP2 PP2 -> TP4 PP1 (bf16, 16 GB each side): every byte against the oracle, streamed per
   tensor group; the benchmark's 2^28-byte buckets, from emu_pack_buckets and from the fused plan, every
   byte against the oracle, and unpacked; then the reverse transition checked as a round trip on the
@@ -92,6 +93,24 @@ def test_1b_tp4_to_tp2(gpu_lib):
     D = p.alloc(1, fill=0xA5, guard=GUARD)
     guarded(lambda: p.reshard(ws, S.ptrs, D.ptrs), S.tensors, [(D.tensors, 0xA5)], "1B reshard")
     check_reshard(p, S, D, label="1B TP4PP1->TP2PP1")
+    del S, D, ws
+    cleanup()
+
+
+def test_odd_widths_written_through(gpu_lib):
+    """A decoder with odd widths, large enough to write through in all three calls: TP1 PP2 -> TP2 PP1 with a padded
+    vocabulary, packed into buckets of an odd number of elements and unpacked; every byte against the oracle."""
+    m = emu.Model(16, 996, 12, 83, 6, 2658, 50257)
+    p = emu.Plan(emu.Layout(m, 1, 2), emu.Layout(m, 2, 1, 64))
+    assert p.info["bytes_read"] + p.info["bytes_written"] >= 1 << 30 and p.info["dst_bytes"] >= 1 << 28
+    ws = p.workspace()
+    S = p.alloc(0, fill=0x5A, guard=GUARD)
+    fill_device(p, 0, S, seed=17)
+    D = p.alloc(1, fill=0xA5, guard=GUARD)
+    guarded(lambda: p.reshard(ws, S.ptrs, D.ptrs), S.tensors, [(D.tensors, 0xA5)], "odd widths")
+    check_reshard(p, S, D, label="odd widths TP1PP2->TP2PP1(pad)")
+    _pack_check(p, ws, D, (1 << 22) + 2, "odd widths: buckets 2^22 + 2")
+    _pack_check(p, ws, D, 1 << 22, "odd widths: buckets 2^22")
     del S, D, ws
     cleanup()
 
@@ -222,7 +241,7 @@ def test_8b_receiver_plans_from_buckets(gpu_lib):
 def test_8b_padded_receiver_plan_phase_shifted(gpu_lib):
     """The padded workload's receiver side: the TP8PP4 (vocabulary padded to TP*128) source set packed
     into 2^28-2-byte buckets, every bucket at another 16-byte phase, and resharded from them straight
-    into TP2PP2 tensors (the byte-granular path at full size) equals emu_reshard's result, which is
+    into TP2PP2 tensors (units at any alignment at full size) equals emu_reshard's result, which is
     checked against the oracle; source pad rows hold random values and must not be read."""
     import torch
 

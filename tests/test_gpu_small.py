@@ -1,6 +1,6 @@
 """GPU parity on small models: every output byte compared with the oracle on the same seeded inputs.
 
-Covers the micro models (which also exercise the byte-granular path: 8-byte o/down runs at TP4), the
+Covers the micro models (which also exercise runs below a 16-byte unit: 8-byte o/down runs at TP4), the
 tiny 2-layer decoder's Split TP1 PP1 -> TP2 PP1 and Merge back, the tiny transition captured in a HIP
 graph and replayed, format changes, padded vocabularies with zero-filled destination pad rows, every
 launch option, and bucket pack/unpack at awkward bucket sizes (including sizes that put source and
@@ -130,7 +130,7 @@ def test_random_layout_pairs(gpu_lib, row_wrap):
     """400 random valid layout pairs on random small models, each with a random bucket size: reshard,
     pack and unpack bit-exact against the oracle, the fused source -> bucket plan giving the same
     buckets, and the receiver plan rebuilding the destination set from the source set's buckets (of
-    another size). Of the 400: 206 have byte-granular segments (odd widths
+    another size). Of the 400: 206 have misaligned segments (odd widths
     put runs at every 16-byte phase), 203 convert between fp32 and bf16, 133 zero-fill pad rows, 177
     replicate KV heads and 141 have uneven pipeline stages. Run once with row-wrapping tiles for 2D
     segments (the default) and once with whole-row tiles and row slices."""

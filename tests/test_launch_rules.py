@@ -138,3 +138,24 @@ def test_buckets_by_set_size(probe):
         for unpack in (False, True):
             assert bucket(probe, p, 1 << 22, unpack) == (THROUGH, 12)
             assert bucket(probe, p, (1 << 22) + 2, unpack) == (policy, 12)
+
+
+def test_the_write_through_tests_write_through(probe):
+    """The plans and sets that the bit-exact tests of writing through run are launched so."""
+    import test_any_alignment as t
+    from test_bucket_pieces import LARGE
+
+    for tile_vecs in (0, 1, 2, 8, 16):
+        with options(TILE_VECS=tile_vecs):
+            for width in t.WIDTHS:
+                for pair in t.PAIRS:
+                    for a, b in ((1, 2), (2, 1)):
+                        p = t.through_plan(width, a, b, pair)
+                        n = t.through_groups(p)
+                        assert n <= 65535 and (p.info["n_general_segments"] > 0 or width in (4, 8))
+                        if (pair, tile_vecs) != (("bf16", "fp32"), 1):  # streams, see reshard_rule
+                            assert reshard(probe, p, n)[0] == THROUGH, (width, pair, tile_vecs)
+    for shape, pad, dtype, sizes in LARGE:
+        lay = emu.Layout(emu.Model(*shape), 2, 1, pad, dtype)
+        p = emu.Plan(lay, lay)
+        assert all(bucket(probe, p, B, unpack)[0] == THROUGH for B in sizes for unpack in (False, True)), (shape, dtype)

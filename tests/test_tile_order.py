@@ -9,13 +9,14 @@ from paper_2609_34645_amd import emu
 @pytest.mark.parametrize("pad", [0, 96])
 def test_maps_around_whole_rounds_of_blocks(gpu_lib, vocab, pad):
     """Maps of about one, two and three rounds of 8 x 256 tiles of 4 KB, a few tiles short of one and past it,
-    with and without a zero-fill section behind the copies."""
+    with and without a zero-fill section behind the copies; streaming, and written through."""
     import torch
+    from test_any_alignment import run_through
 
     m = emu.Model(1, 64, 2, 32, 2, 64, vocab)
     plan = emu.Plan(emu.Layout(m, 1, 1), emu.Layout(m, 1, 1, pad))
     ws = plan.workspace()
-    S, D = plan.alloc(0), plan.alloc(1, fill=0xA5)
+    S, D = plan.alloc(0, guard=256), plan.alloc(1, fill=0xA5, guard=256)
     g = torch.Generator(device="cuda")
     g.manual_seed(vocab)
     for b in S.bufs:
@@ -26,3 +27,4 @@ def test_maps_around_whole_rounds_of_blocks(gpu_lib, vocab, pad):
     for s, d in zip(S.tensors, D.tensors):
         assert torch.equal(d[:s.numel()], s)
         assert not bool(d[s.numel():].any())
+    run_through(plan, ws, S, D)
