@@ -446,7 +446,7 @@ __device__ __forceinline__ void tile_any(const uint8_t* s, uint8_t* d, uint32_t 
   s = ZERO ? nullptr : s - any_src<CVT>(kAnyBias);
   d -= kAnyBias;
 #pragma nounroll
-  for (uint32_t b = 0; b < cnt; b += uint32_t(kReshardThreads) * P) {  // one pass, two for a run's longer last tile
+  for (uint32_t b = 0; b < cnt; b += uint32_t(kReshardThreads) * P) {  // ceil(cnt / (64 P)) passes
     uint32_t to[P];
     bool live[P];
     std::conditional_t<CVT == CVT_BF16_F32 && !ZERO, v2u, v4u> r[P];
@@ -585,7 +585,7 @@ __device__ __forceinline__ void run_tile(const DevSeg& g, uint64_t lt, const uin
     const uint8_t* s = ZERO ? nullptr : sb + g.src_off + uint64_t(q0) * g.src_stride;
     uint8_t* d = db + g.dst_off + uint64_t(q0) * g.dst_stride;
     // A row's first unit on the grid is among its first 128 bytes of units, and its last among the last 256:
-    // a row has up to gmask + 15 bytes more of units than of data, rounded up to the grid.
+    // a row has less than 256 bytes more of units than of data.
     if (r0 * D >= 128 && (r0 + TU) * D + 256 <= g.rv * D) {
       const uint32_t at = r0 * D - (uint32_t(reinterpret_cast<uintptr_t>(d)) & gmask);
       tile_inner<U, POL, ZERO, CVT>(s + any_src<CVT>(at), d + at);

@@ -609,9 +609,9 @@ static int finalize(Plan& P) {
     uint64_t nt;
     if (!vec) {
       // A row's units sit on the destination's address grid: 128 bytes (a cache line) for rows of 2 KB and
-      // more, where the up to 15 units it adds to a row are few; 16 bytes for shorter rows. rv counts a
-      // row's units at the worst phase of its first byte. Rows run in one sequence only if that takes no
-      // more tiles than slices of single rows.
+      // more, where the less than 256 bytes of units it adds to a row are few; 16 bytes for shorter rows. rv
+      // counts a row's units at the worst phase of its first byte. Rows run in one sequence only if that takes
+      // no more tiles than slices of single rows.
       const uint64_t unit = zero ? 16 : any_unit_bytes(P.cvt);
       const uint64_t grid = g.run >= 2048 ? 128 : 16;
       const uint64_t rv0 = (g.run + grid - esd + unit - 1) / unit, per = grid / unit;
