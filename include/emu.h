@@ -200,9 +200,10 @@ typedef enum {
                                 per compute unit, 1..32, enforced by reserving LDS per workgroup (the
                                 LDS is split in two halves, so odd caps above 1 round down to even);
                                 0 = no cap; -1 = automatic (default): 48 KB of reshard tiles (12 of
-                                4 KB, 6 of 8 KB), for fp32 -> bf16 plans 24 KB, for large bf16 -> fp32
-                                plans 56 KB, and 40 or 48 KB of pack/unpack chunks (10 or 12 of 4 KB);
-                                at least 2 (4 in converting plans), no cap from 32 up.
+                                4 KB, 6 of 8 KB), for fp32 -> bf16 plans 24 KB, or 40 KB where an eighth
+                                of the bytes or more is misaligned, for large bf16 -> fp32 plans 56 KB,
+                                and 40 or 48 KB of pack/unpack chunks (10 or 12 of 4 KB); at least
+                                2 (4 in converting plans), no cap from 32 up.
                                 Bounds the bytes in flight per CU, which sets how well HBM serves a
                                 read/write stream */
   EMU_OPT_ROW_WRAP = 7       /* 1 = tile 2D segments as one row-major vector sequence, rows wrapping

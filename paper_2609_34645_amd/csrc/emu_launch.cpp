@@ -20,10 +20,11 @@ static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
 //  - Residency (flight, destination bytes in flight per CU). Copies: 48 KB; 8 / 10 / 12 / 14 tiles ran the 1B
 //    TP4 -> TP2 reshard in 912 / 890 / 890 / 900 us and a decoder with odd widths in 155 / 147 / 145 / 148.
 //    fp32 -> bf16, which reads twice what it writes: 24 KB; 4 / 6 / 8 / 10 tiles took 1548 / 1319 / 1340 / 1355 us
-//    on aligned 1B shards, and with units at any alignment 248 / 211 / 213 / 214 (odd widths, 1.4 GB) and 2377 /
-//    2072 / 2108 / 2115 (8 layers of the 8B decoder into odd buckets). bf16 -> fp32, which reads half: written
-//    through 56 KB, 12 / 14 / 16 tiles in 1377 / 1364 / 1372 us (1B, fused to separate formats), with plain stores
-//    56 KB, 10 / 12 / 14 / 16 in 1623 / 1498 / 1459 / 1461, streaming 48 KB, in 1414 / 1382 / 1394 / 1418.
+//    on aligned 1B shards. From an eighth of the bytes at any alignment on 40 KB: with 6 tiles a first pass over new
+//    buffers takes 250 us against 241 (odd widths, 1.4 GB) and sets of 23 and 36 MB 6.2 and 7.9 against 5.7 and 7.5,
+//    more than the 211 against 215 us that later passes gain. bf16 -> fp32, which reads half: written through 56 KB,
+//    12 / 14 / 16 tiles in 1377 / 1364 / 1372 us (1B, fused to separate formats), with plain stores 56 KB, 10 / 12 /
+//    14 / 16 in 1623 / 1498 / 1459 / 1461, streaming 48 KB, in 1414 / 1382 / 1394 / 1418.
 //    Conversions keep at least 4 of the larger tiles: 2 / 4 / 6 took 1895 / 1378 / 1447 us at 8 KB (fp32 -> bf16),
 //    1776 / 1473 / 1527 at 16 KB, and 1637 / 1391 / 1447 for bf16 -> fp32 at 16 KB. Copies at 16 KB run best with
 //    2: 929 / 974 / 1009.
@@ -33,21 +34,20 @@ static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
 //    107.2 against 105.5; 4 MB: 2.7 against 2.5). Conversions: by the share of their bytes at any alignment, with
 //    the line at an eighth. Written through / streaming, fp32 -> bf16 at a share of 0 / 0.006 / 0.22 / 0.67 / 0.8:
 //    1070 / 1079, 992 / 1002, 1089 / 1088, 1113 / 1096 and 447 / 443 us; bf16 -> fp32 at 0 / 0.006 / 0.22 / 0.67:
-//    1104 / 1108, 1017 / 1028, 1119 / 1116 and 1133 / 1127. Widening at 1 KB tiles, whose
-//    residency has no cap, streams: 1601 us against 1635 (without a cap at 4 KB, 1559 against 1518: the option alone
-//    does not decide it).
+//    1104 / 1108, 1017 / 1028, 1119 / 1116 and 1133 / 1127. Widening at 1 KB tiles
+//    streams: 1601 us against 1635.
 constexpr uint64_t kThroughBytes = 1ull << 30;  // read and written by one reshard launch
 
 LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
   const uint64_t moved = (P.info.bytes_read + P.info.bytes_written) * groups;
   const bool whole = P.cvt == CVT_NONE || P.any_bytes < P.info.bytes_written / 8;
-  const int least = P.cvt == CVT_NONE ? 2 : 4;
-  const auto cap = [&](uint64_t kb) { return resident(P.tile_bytes, kb << 10, least); };
-  const LaunchRule stream{POL_NT, cap(P.cvt == CVT_F32_BF16 ? 24 : 48)};
-  const LaunchRule through{POL_THROUGH, cap(P.cvt == CVT_F32_BF16 ? 24 : P.cvt == CVT_BF16_F32 ? 56 : 48)};
-  if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, through.cap};
   const bool thin = P.cvt == CVT_BF16_F32 && P.tile_vecs == 1;
-  return moved >= kThroughBytes && whole && !thin ? through : stream;
+  int policy = POL_PLAIN;
+  if (option(EMU_OPT_NONTEMPORAL) != 0) policy = moved >= kThroughBytes && whole && !thin ? POL_THROUGH : POL_NT;
+  uint64_t flight = 48 << 10;
+  if (P.cvt == CVT_F32_BF16) flight = (whole ? 24 : 40) << 10;
+  else if (P.cvt == CVT_BF16_F32 && policy != POL_NT) flight = 56 << 10;
+  return {policy, resident(P.tile_bytes, flight, P.cvt == CVT_NONE ? 2 : 4)};
 }
 
 // Pack and unpack cut chunks on the stream's grid unless the destination's differs: buckets whose size is not

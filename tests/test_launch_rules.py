@@ -78,7 +78,7 @@ def test_reshard_by_bytes_moved(probe):
         assert reshard(probe, big) == (THROUGH, 7)
 
 
-@pytest.mark.parametrize("pair, few, many", [(("fp32", "bf16"), (THROUGH, 6), (NT, 6)),
+@pytest.mark.parametrize("pair, few, many", [(("fp32", "bf16"), (THROUGH, 6), (NT, 10)),
                                              (("bf16", "fp32"), (THROUGH, 14), (NT, 12))], ids=["narrow", "widen"])
 def test_conversions_by_share_of_misaligned_bytes(probe, pair, few, many):
     """One misaligned segment does not change how the rest of a large converting plan is launched: the share of
