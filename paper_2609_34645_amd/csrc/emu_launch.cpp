@@ -63,21 +63,19 @@ bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack) {
 // 2^28 - 4: 4,792 against 4,797), and tensors off the 4 KB grid the pack's, whatever the buckets (odd widths in
 // 4 MB buckets, 2.3 GB: 708 us against 722).
 //
-// Written through / streaming, with sets in rotation that no cache holds. Buckets on the 4 KB grid, unpack 10.97 /
-// 10.84 us (a set of 26 MB), 17.6 / 18.3 (49 MB), 25.2 / 25.8 (75), 40.1 / 41.6 (128), 95.3 / 98.8 (317), 901 / 936
-// (3.0 GB, pack 900 / 941), with odd widths 25.6 / 26.1 (76 MB), 64.1 / 65.8 (207). A set and its buckets that fit
-// the last-level cache (256 MB) and are moved again stream better: pack 40.9 / 40.3 (125 MB), so the line lies there.
-// Other bucket sizes, where pieces stored under lane masks lose what the others gain, unpack 25.9 / 25.9 (76 MB),
-// 39.0 / 39.0 (120), 65.3 / 65.2 (207, pack 65.9 / 65.6), 91.7 / 91.9 (295, pack 92.2 / 92.3), 174 / 176 (557).
-constexpr uint64_t kThroughGrid = 1ull << 28;   // read and written by one pack or unpack, buckets on the grid
-constexpr uint64_t kThroughOther = 1ull << 29;  // other bucket sizes
+// Written through / streaming. Sets in rotation that no cache holds, buckets on the 4 KB grid, unpack: 10.97 /
+// 10.84 us (a set of 26 MB), 40.1 / 41.6 (128), 95.3 / 98.8 (317), 901 / 936 (3.0 GB, pack 900 / 941). Other bucket
+// sizes, where pieces stored under lane masks lose what the others gain: 39.0 / 39.0 (120 MB), 65.3 / 65.2 (207, pack
+// 65.9 / 65.6), 91.7 / 91.9 (295, pack 92.2 / 92.3), 174 / 176 (557). The same set again and again, part of which the
+// last-level cache keeps, streams better below the line: pack 40.9 / 40.3 (125 MB), unpack 59.6 / 58.2 (190 MB in
+// tensors of 86 KB), 75.9 / 73.9 (235).
+constexpr uint64_t kThroughBucketBytes = 1ull << 29;  // read and written by one pack or unpack
 
 LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack) {
   const bool shifted = !s.offsets_grid || chunks_realign(s, B, unpack) || B % 4 != 0;
-  const int cap = resident(kTileChunkBytes, (shifted ? 48 : 40) << 10);
-  if (option(EMU_OPT_NONTEMPORAL) == 0) return {POL_PLAIN, cap};
-  const uint64_t from = B % kTileChunkBytes == 0 ? kThroughGrid : kThroughOther;
-  return {2 * s.total_bytes >= from ? POL_THROUGH : POL_NT, cap};
+  int policy = POL_PLAIN;
+  if (option(EMU_OPT_NONTEMPORAL) != 0) policy = 2 * s.total_bytes >= kThroughBucketBytes ? POL_THROUGH : POL_NT;
+  return {policy, resident(kTileChunkBytes, (shifted ? 48 : 40) << 10)};
 }
 
 }  // namespace emu

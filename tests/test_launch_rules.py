@@ -126,18 +126,11 @@ def test_buckets_by_set_size(probe):
         assert bucket(probe, big, (1 << 28) - 2, unpack) == (THROUGH, 12)
         with options(NONTEMPORAL=0):
             assert bucket(probe, big, 1 << 28, unpack) == (PLAIN, 10)
-    # sets of 128 and 152 MB: buckets on the 4 KB grid write through from 134 MB on, others from 268 MB
-    for shape, policy in (((4, 1024, 16, 64, 8, 2816, 8192), NT), ((5, 1024, 16, 64, 8, 2816, 8192), THROUGH)):
-        p = plan(shape, (2, 1), (2, 1))
-        for unpack in (False, True):
-            assert bucket(probe, p, 1 << 24, unpack) == (policy, 12)
-            assert bucket(probe, p, (1 << 24) - 2, unpack) == (NT, 12)
-    for layers, policy in ((3, NT), (4, THROUGH)):
+    for layers, policy in ((3, NT), (4, THROUGH)):  # sets of 266 and 288 MB: from 2^28 bytes on, whatever the buckets
         p = plan((layers, 996, 12, 83, 6, 2658, 50257), (2, 1), (2, 1), pads=(64, 64))
         assert (p.info["src_bytes"] >= 1 << 28) == (policy == THROUGH)
         for unpack in (False, True):
-            assert bucket(probe, p, 1 << 22, unpack) == (THROUGH, 12)
-            assert bucket(probe, p, (1 << 22) + 2, unpack) == (policy, 12)
+            assert bucket(probe, p, 1 << 22, unpack) == bucket(probe, p, (1 << 22) + 2, unpack) == (policy, 12)
 
 
 def test_the_write_through_tests_write_through(probe):
