@@ -31,21 +31,28 @@ static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
 //  - Cache policy. Writing through gains from about 1 GB moved per launch on (1B copy 890 against 914 us, 8B 4823
 //    against 4928, fp32 -> bf16 1319 against 1335, bf16 -> fp32 1364 against 1382; copies with units at any alignment:
 //    odd widths, 4.8 GB, 724 against 743, 8B into and out of odd buckets 10.12 against 10.28 ms), not below (0.7 GB:
-//    107.2 against 105.5; 4 MB: 2.7 against 2.5). Conversions: by the share of their bytes at any alignment, with
-//    the line at an eighth. Written through / streaming, fp32 -> bf16 at a share of 0 / 0.006 / 0.22 / 0.67 / 0.8:
-//    1070 / 1079, 992 / 1002, 1089 / 1088, 1113 / 1096 and 447 / 443 us; bf16 -> fp32 at 0 / 0.006 / 0.22 / 0.67:
-//    1104 / 1108, 1017 / 1028, 1119 / 1116 and 1133 / 1127. Widening at 1 KB tiles
-//    streams: 1601 us against 1635.
+//    107.2 against 105.5; 4 MB: 2.7 against 2.5). Conversions at any alignment: written through
+//    / streaming, fp32 -> bf16 at a share of 0 / 0.006 / 0.22 / 0.67 / 0.8 of the bytes 1070 / 1079, 992 / 1002, 1089 /
+//    1088, 1113 / 1096 and 447 / 443 us; bf16 -> fp32 at 0 / 0.006 / 0.22 / 0.67: 1104 / 1108, 1017 / 1028, 1119 /
+//    1116 and 1133 / 1127. Widening at 1 KB tiles streams: 1601 us against 1635.
+//    Tiles that end inside a 64-byte granule (whole vectors, but destination offsets or strides off the granule) are
+//    written to memory in two parts, where streaming stores meet in the L2. Copies at such a share of 0.18 / 0.22 /
+//    0.28 / 0.28 / 0.48 / 0.60: 464 / 467, 588 / 588, 455 / 461, 950 / 936, 973 / 931 and 629 / 591, 8B into buckets
+//    of 2^28 - 16 bytes (0.6) 5,514 / 5,030. fp32 -> bf16 at 0.06 / 0.18 / 0.22 / 0.28 / 0.48: 651 / 648, 701 / 679,
+//    881 / 844, 1,466 / 1,356 and 1,508 / 1,359; bf16 -> fp32 at 0.06 / 0.11 / 0.18 / 0.22 / 0.44: 670 / 668, 1,443 /
+//    1,416, 716 / 697, 908 / 878 and 1,584 / 1,455. So copies write through up to a third, conversions up to a tenth,
+//    bytes at any alignment counted in.
 constexpr uint64_t kThroughBytes = 1ull << 30;  // read and written by one reshard launch
 
 LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
   const uint64_t moved = (P.info.bytes_read + P.info.bytes_written) * groups;
-  const bool whole = P.cvt == CVT_NONE || P.any_bytes < P.info.bytes_written / 8;
+  const uint64_t written = P.info.bytes_written;
   const bool thin = P.cvt == CVT_BF16_F32 && P.tile_vecs == 1;
+  const bool whole = P.cvt == CVT_NONE ? P.off_bytes <= written / 3 : P.any_bytes + P.off_bytes <= written / 10;
   int policy = POL_PLAIN;
   if (option(EMU_OPT_NONTEMPORAL) != 0) policy = moved >= kThroughBytes && whole && !thin ? POL_THROUGH : POL_NT;
   uint64_t flight = 48 << 10;
-  if (P.cvt == CVT_F32_BF16) flight = (whole ? 24 : 40) << 10;
+  if (P.cvt == CVT_F32_BF16) flight = (P.any_bytes < written / 8 ? 24 : 40) << 10;
   else if (P.cvt == CVT_BF16_F32 && policy != POL_NT) flight = 56 << 10;
   return {policy, resident(P.tile_bytes, flight, P.cvt == CVT_NONE ? 2 : 4)};
 }

@@ -594,7 +594,7 @@ static int finalize(Plan& P) {
   const uint64_t salign = P.cvt == CVT_BF16_F32 ? 8 : 16;
   const uint64_t esd = uint64_t(elem_size(P.side[1].lay.dtype));
   int32_t ngeneral = 0;
-  P.any_bytes = 0;
+  P.any_bytes = P.off_bytes = 0;
   const bool row_wrap = option(EMU_OPT_ROW_WRAP) != 0;
   for (size_t i = 0; i < P.segs.size(); ++i) {
     const emu_segment_t& g = P.segs[i];
@@ -660,6 +660,8 @@ static int finalize(Plan& P) {
       d.param = uint32_t(tpr);
       nt = g.rows * tpr;
     }
+    const bool apart = g.rows > 1 && g.dst_stride != g.run;  // rows that do not follow each other
+    if (vec && !zero && (g.dst_offset % 64 || (apart && (g.dst_stride | g.run) % 64))) P.off_bytes += g.rows * g.run;
     if (zero) {
       d.mode |= SEG_ZERO;
       zero_bytes += g.rows * g.run;

@@ -103,6 +103,21 @@ def test_residency_at_other_tile_sizes(probe, tile_vecs, copy, narrow, widen):
         assert reshard(probe, plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32"))[1] == widen
 
 
+def test_tiles_that_end_inside_a_granule(probe):
+    """Buckets whose size is a multiple of a vector but not of 64 bytes put most of a fused plan's tiles off the
+    granule; a size that is keeps them on it, at any phase of a 128-byte line."""
+    for pair, cap in ((("bf16", "bf16"), (12, 12)), (("fp32", "bf16"), (6, 6)), (("bf16", "fp32"), (14, 12))):
+        for B, want in (((1 << 26) - 64, (THROUGH, cap[0])), ((1 << 26) - 16, (NT, cap[1]))):
+            p = plan(ONE_B, (4, 1), (2, 1), *pair, bucket_bytes=B)
+            assert p.info["n_general_segments"] == 0 and reshard(probe, p) == want, (pair, B)
+    # row slices off the granule, 22% of the bytes in the Merge: copies still write through, conversions do not;
+    # in the Split each slice is a whole tensor
+    shape = (6, 3144, 12, 20, 6, 10512, 52648)
+    for pair, want in ((("bf16", "bf16"), THROUGH), (("fp32", "bf16"), NT), (("bf16", "fp32"), NT)):
+        assert reshard(probe, plan(shape, (2, 1), (1, 1), *pair))[0] == want
+        assert reshard(probe, plan(shape, (1, 1), (2, 1), *pair))[0] == THROUGH
+
+
 def test_write_through_without_a_cap(probe):
     big, wide = plan(ONE_B, (4, 1), (2, 1)), plan(ONE_B, (4, 1), (2, 1), "bf16", "fp32")
     with options(WG_PER_CU=0):
