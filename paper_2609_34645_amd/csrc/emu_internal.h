@@ -103,6 +103,7 @@ struct SideInfo {
   int32_t nranks = 0;
   uint64_t total_bytes = 0;
   bool offsets_grid = true;           // every tensor's stream offset is a multiple of kTileChunkBytes
+  bool offsets_dword = true;          // or at least of 4
   std::vector<emu_tensor_desc_t> tensors;
   std::vector<uint32_t> rank_first;   // nranks + 1
   std::vector<uint64_t> rank_bytes;   // nranks

@@ -67,8 +67,8 @@ bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack) {
 // 10,087 us for the 8B pack and unpack, whose chunks end on tensor and bucket ends; 298 / 288 / 292 us where
 // chunks are moved to the destination's grid and hold several pieces (odd widths). Buckets that start inside a
 // dword make the unpack's loads slower: 12 per CU there too (8B at 2^28 - 2: 4,838 us against 4,943 at 10; at
-// 2^28 - 4: 4,792 against 4,797), and tensors off the 4 KB grid the pack's, whatever the buckets (odd widths in
-// 4 MB buckets, 2.3 GB: 708 us against 722).
+// 2^28 - 4: 4,792 against 4,797), and tensors that do the pack's, whatever the buckets (odd widths in 4 MB buckets,
+// 2.3 GB: 708 us against 722; at tensors off the 4 KB grid, but on dwords, 715 against 702).
 //
 // Written through / streaming. Sets in rotation that no cache holds, buckets on the 4 KB grid, unpack: 10.97 /
 // 10.84 us (a set of 26 MB), 40.1 / 41.6 (128), 95.3 / 98.8 (317), 901 / 936 (3.0 GB, pack 900 / 941). Other bucket
@@ -79,7 +79,7 @@ bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack) {
 constexpr uint64_t kThroughBucketBytes = 1ull << 29;  // read and written by one pack or unpack
 
 LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack) {
-  const bool shifted = !s.offsets_grid || chunks_realign(s, B, unpack) || B % 4 != 0;
+  const bool shifted = chunks_realign(s, B, unpack) || B % 4 != 0 || !s.offsets_dword;
   int policy = POL_PLAIN;
   if (option(EMU_OPT_NONTEMPORAL) != 0) policy = 2 * s.total_bytes >= kThroughBucketBytes ? POL_THROUGH : POL_NT;
   return {policy, resident(kTileChunkBytes, (shifted ? 48 : 40) << 10)};

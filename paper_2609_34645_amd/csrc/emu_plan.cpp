@@ -231,12 +231,13 @@ static int build_side(const emu_layout_t& lay, SideInfo& s, std::vector<std::vec
   s.rank_bytes.assign(s.nranks, 0);
   s.chunk_first.assign(s.nranks + 1, 0);
   s.total_bytes = 0;
-  s.offsets_grid = true;
+  s.offsets_grid = s.offsets_dword = true;
   for (int r = 0; r < s.nranks; ++r) {
     uint64_t off = 0;
     for (uint32_t i = s.rank_first[r]; i < s.rank_first[r + 1]; ++i) {
       s.tensors[i].stream_offset = off;
       s.offsets_grid = s.offsets_grid && off % kTileChunkBytes == 0;
+      s.offsets_dword = s.offsets_dword && off % 4 == 0;
       off += s.tensors[i].bytes;
     }
     s.rank_bytes[r] = off;
@@ -368,6 +369,7 @@ static SideInfo bucket_side(const SideInfo& X, uint64_t B) {
   bk.nranks = X.nranks;
   bk.total_bytes = X.total_bytes;
   bk.offsets_grid = B % kTileChunkBytes == 0 || X.nranks == 0;
+  bk.offsets_dword = B % 4 == 0 || X.nranks == 0;
   bk.rank_first.assign(X.nranks + 1, 0);
   bk.rank_bytes = X.rank_bytes;
   bk.chunk_first.assign(X.nranks + 1, 0);
