@@ -619,16 +619,14 @@ __device__ __forceinline__ void run_tile(const DevSeg& g, uint64_t lt, const uin
 // One workgroup per tile. The dispatcher deals workgroups to the XCDs round-robin; with XCD remapping, XCD x
 // takes blocks x, x + 8, ... of kReshardBlock consecutive tiles (1 MB at 4 KB tiles), so each XCD's L2 sees
 // whole blocks and the eight of them work through one front of the map; what is left after the last whole
-// round of blocks goes to the XCDs in contiguous eighths. On the same buffers, 1B TP4 -> TP2 / the same in
+// round of blocks, or all of a map that reshard_rule gives no blocks, goes to the XCDs in contiguous eighths. On the same buffers, 1B TP4 -> TP2 / the same in
 // fp32, three groups / 8B TP2 PP2 -> TP4: 885 / 5356 / 4822 us against 901 / 5398 / 4799 with contiguous
 // eighths of the whole map; blocks of 512 tiles 887 / 5372 / 4812, of 1024 891 / 5370 / 4816.
 //
 // The map holds the copy segments' tiles, then the zero-fill segments' (padded vocabulary rows); both run in
 // one launch: a launch of its own took the zero fill 4 to 5 us, whatever its size.
-constexpr uint32_t kReshardBlock = 256;
-
-__device__ __forceinline__ uint32_t xcd_tile(uint32_t w, uint32_t per) {  // per: an eighth of the grid
-  const uint32_t x = w % kXcds, j = w / kXcds, whole = per / kReshardBlock * kReshardBlock;
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t w, uint32_t per, uint32_t whole) {  // per: an eighth of the
+  const uint32_t x = w % kXcds, j = w / kXcds;                                              // grid; whole: in blocks
   if (j < whole) return ((j / kReshardBlock) * kXcds + x) * kReshardBlock + j % kReshardBlock;
   return whole * kXcds + x * (per - whole) + (j - whole);
 }
@@ -636,6 +634,7 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t w, uint32_t per) {  // per
 template <int U, int POL, bool LDS, bool XCD, int CVT>
 __global__ __launch_bounds__(kReshardThreads, EMU_RESHARD_WAVES_PER_EU) void k_reshard(const uint32_t* __restrict__ tilemap,
                                                                              uint32_t tile_base, uint32_t per,
+                                                                             uint32_t whole,
                                                                              const DevSeg* __restrict__ segs,
                                                                              const uint64_t* __restrict__ dst_ptrs,
                                                                              const uint64_t* __restrict__ src_ptrs,
@@ -646,7 +645,7 @@ __global__ __launch_bounds__(kReshardThreads, EMU_RESHARD_WAVES_PER_EU) void k_r
   // after the descriptor, also where a zero fill will not use it (entry 0 then): the chain before the first
   // data load is map entry, descriptor, pointers. The arguments are in registers when a wave starts (the
   // build asks for them to be preloaded).
-  const uint32_t tile = tile_base + (XCD ? xcd_tile(blockIdx.x, per) : blockIdx.x);
+  const uint32_t tile = tile_base + (XCD ? xcd_tile(blockIdx.x, per, whole) : blockIdx.x);
   const uint32_t si = tilemap[tile];
   if (si == kNoSeg) return;
   const DevSeg g = segs[si];
@@ -1035,6 +1034,7 @@ struct ReshardLaunch {
   const uint32_t* tm;
   uint64_t n_map;
   int cap;
+  bool blocks;
   Tables tb;
   hipStream_t st;
 };
@@ -1046,9 +1046,9 @@ static void launch_reshard(const ReshardLaunch& l) {
   // a multiple of kXcds whose work-items (64 per workgroup) stay below 2^32 in the grid's x dimension
   constexpr uint64_t kMaxGrid = (1ull << 26) - kXcds;
   for (uint64_t done = 0; done < l.n_map; done += kMaxGrid) {
-    const uint32_t grid = uint32_t(l.n_map - done < kMaxGrid ? l.n_map - done : kMaxGrid);
+    const uint32_t grid = uint32_t(l.n_map - done < kMaxGrid ? l.n_map - done : kMaxGrid), per = grid / kXcds;
     hipLaunchKernelGGL((k_reshard<U, POL, LDS, XCD, CVT>), dim3(grid, l.tb.groups), dim3(kReshardThreads), lds, l.st,
-                       l.tm, uint32_t(done), grid / kXcds, l.segs, l.tb.dp, l.tb.sp, l.tb.dst_n, l.tb.src_n);
+                       l.tm, uint32_t(done), per, l.blocks ? per / kReshardBlock * kReshardBlock : 0u, l.segs, l.tb.dp, l.tb.sp, l.tb.dst_n, l.tb.src_n);
   }
 }
 
@@ -1162,7 +1162,7 @@ static int launch_plan(const Plan* P, const uint8_t* w, const uint64_t* sp, cons
                        hipStream_t st, const char* what) {
   const LaunchRule rule = reshard_rule(*P, groups);
   const ReshardLaunch l{reinterpret_cast<const DevSeg*>(w + P->ws.off_segs),
-                        reinterpret_cast<const uint32_t*>(w + P->ws.off_tilemap), P->ws.n_map, rule.cap,
+                        reinterpret_cast<const uint32_t*>(w + P->ws.off_tilemap), P->ws.n_map, rule.cap, rule.blocks,
                         Tables{sp, dp, groups, uint32_t(P->side[0].tensors.size()), uint32_t(P->side[1].tensors.size())}, st};
   drop_pending_error();
   switch (P->tile_vecs) {

@@ -25,6 +25,7 @@ constexpr uint64_t kTileChunkBytes = EMU_TILE_CHUNK_BYTES;  // unit of the tile-
 constexpr uint32_t kMapTensorBits = 20;            // chunk map entry: rank << 20 | global tensor index
 constexpr uint64_t kWsAlign = 256;
 constexpr uint32_t kXcdCount = 8;          // XCDs of an MI355X; reshard grids are a multiple of this
+constexpr uint32_t kReshardBlock = 256;    // consecutive reshard tiles of one XCD, where it takes blocks
 constexpr uint32_t kNoSeg = 0xffffffffu;   // tile map padding entry: the workgroup has no tile
 
 // Segment execution modes. Every "vec" mode needs src/dst offsets, strides and the run to be
@@ -137,10 +138,12 @@ struct Plan {
 // Cache policies of the kernels' loads and stores: plain, streaming, streaming and written through.
 enum Policy : int { POL_PLAIN = 0, POL_NT = 1, POL_THROUGH = 2 };
 
-// How one call is launched (emu_launch.cpp): the policy, and the most workgroups resident per CU (0: no cap).
+// How one call is launched (emu_launch.cpp): the policy, the most workgroups resident per CU (0: no cap), and
+// whether the reshard's XCDs take blocks of tiles or contiguous eighths of the map.
 struct LaunchRule {
   int policy;
   int cap;
+  bool blocks;
 };
 LaunchRule reshard_rule(const Plan& P, uint32_t groups);
 bool chunks_realign(const SideInfo& s, uint64_t B, bool unpack);

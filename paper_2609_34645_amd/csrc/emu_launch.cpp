@@ -42,7 +42,13 @@ static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
 //    881 / 844, 1,466 / 1,356 and 1,508 / 1,359; bf16 -> fp32 at 0.06 / 0.11 / 0.18 / 0.22 / 0.44: 670 / 668, 1,443 /
 //    1,416, 716 / 697, 908 / 878 and 1,584 / 1,455. So copies write through up to a third, conversions up to a tenth,
 //    bytes at any alignment counted in.
+//  - Order. Blocks of kReshardBlock tiles from four rounds over the XCDs on (8,192 tiles), contiguous eighths of the
+//    map below, where the front of one to three rounds leaves XCDs idle at its end: three states in rotation, in
+//    blocks / eighths, 2,789 tiles 5.28 / 4.72 us, 3,371 tiles 6.45 / 6.04, 5,321 tiles 9.04 / 8.62, 7,009 tiles 11.05 /
+//    11.03, 10,385 tiles 15.3 / 15.1 (a Merge 15.6 / 15.9), 17,137 tiles 23.5 / 23.7. Tiles at any alignment take longer
+//    than others, and eighths deal them unevenly: blocks there, 7,945 tiles 13.55 / 13.95, 7,636 tiles 12.8 / 13.2.
 constexpr uint64_t kThroughBytes = 1ull << 30;  // read and written by one reshard launch
+constexpr uint64_t kBlockTiles = 4 * kXcdCount * kReshardBlock;
 
 LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
   const uint64_t moved = (P.info.bytes_read + P.info.bytes_written) * groups;
@@ -54,7 +60,7 @@ LaunchRule reshard_rule(const Plan& P, uint32_t groups) {
   uint64_t flight = 48 << 10;
   if (P.cvt == CVT_F32_BF16) flight = (P.any_bytes < written / 8 ? 24 : 40) << 10;
   else if (P.cvt == CVT_BF16_F32 && policy != POL_NT) flight = 56 << 10;
-  return {policy, resident(P.tile_bytes, flight, P.cvt == CVT_NONE ? 2 : 4)};
+  return {policy, resident(P.tile_bytes, flight, P.cvt == CVT_NONE ? 2 : 4), P.ws.n_map >= kBlockTiles || P.any_bytes > 0};
 }
 
 // Pack and unpack cut chunks on the stream's grid unless the destination's differs: buckets whose size is not
@@ -82,7 +88,7 @@ LaunchRule bucket_rule(const SideInfo& s, uint64_t B, bool unpack) {
   const bool shifted = chunks_realign(s, B, unpack) || B % 4 != 0 || !s.offsets_dword;
   int policy = POL_PLAIN;
   if (option(EMU_OPT_NONTEMPORAL) != 0) policy = 2 * s.total_bytes >= kThroughBucketBytes ? POL_THROUGH : POL_NT;
-  return {policy, resident(kTileChunkBytes, (shifted ? 48 : 40) << 10)};
+  return {policy, resident(kTileChunkBytes, (shifted ? 48 : 40) << 10), true};
 }
 
 }  // namespace emu

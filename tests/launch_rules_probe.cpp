@@ -7,6 +7,7 @@ extern "C" void probe_reshard(const void* plan, uint32_t groups, int32_t* out) {
   const emu::LaunchRule r = emu::reshard_rule(*static_cast<const emu::Plan*>(plan), groups);
   out[0] = r.policy;
   out[1] = r.cap;
+  out[2] = r.blocks;
 }
 
 extern "C" void probe_bucket(const void* plan, int32_t side, uint64_t B, int32_t unpack, int32_t* out) {

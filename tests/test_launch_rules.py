@@ -52,9 +52,15 @@ def plan(shape, src, dst, sdt="bf16", ddt="bf16", pads=(0, 0), **kw):
 
 
 def reshard(probe, p, groups=1):
-    out = (ctypes.c_int32 * 2)()
+    out = (ctypes.c_int32 * 3)()
     probe.probe_reshard(p._h, groups, out)
-    return tuple(out)
+    return tuple(out)[:2]
+
+
+def in_blocks(probe, p):
+    out = (ctypes.c_int32 * 3)()
+    probe.probe_reshard(p._h, 1, out)
+    return bool(out[2])
 
 
 def bucket(probe, p, B, unpack, side=0):
@@ -116,6 +122,16 @@ def test_tiles_that_end_inside_a_granule(probe):
     for pair, want in ((("bf16", "bf16"), THROUGH), (("fp32", "bf16"), NT), (("bf16", "fp32"), NT)):
         assert reshard(probe, plan(shape, (2, 1), (1, 1), *pair))[0] == want
         assert reshard(probe, plan(shape, (1, 1), (2, 1), *pair))[0] == THROUGH
+
+
+def test_order_by_tiles(probe):
+    """Maps of fewer than four rounds of blocks go in contiguous eighths, unless some of their tiles are misaligned."""
+    for vocab, blocks in ((4 * 32 * 1024 - 1000, False), (4 * 32 * 1024, True)):
+        p = plan((1, 64, 2, 32, 2, 64, vocab), (1, 1), (1, 1), pads=(0, 96))
+        assert (p.info["n_tiles"] >= 8192) == blocks and in_blocks(probe, p) == blocks
+    assert not in_blocks(probe, plan((6, 256, 8, 32, 4, 864, 1024), (2, 1), (1, 1)))
+    p = plan((6, 250, 8, 32, 4, 864, 1024), (2, 1), (1, 1))
+    assert p.info["n_general_segments"] > 0 and p.info["n_tiles"] < 8192 and in_blocks(probe, p)
 
 
 def test_write_through_without_a_cap(probe):
