@@ -186,8 +186,9 @@ typedef enum {
                                 threads per workgroup): 1, 2, 4, 8 or 16 (1 to 16 KB tiles), or 0 =
                                 automatic (default): 4 (4 KB tiles). Read by emu_plan, so a plan
                                 keeps its tile size */
-  EMU_OPT_XCD_REMAP = 1,     /* 1 = give each XCD whole blocks of consecutive reshard tiles instead of
-                                every eighth tile (default 1) */
+  EMU_OPT_XCD_REMAP = 1,     /* 1 = give each XCD whole blocks of consecutive reshard tiles, or one
+                                contiguous eighth of a small map, instead of every eighth tile
+                                (default 1) */
   EMU_OPT_NONTEMPORAL = 2,   /* 1 = streaming (non-temporal) loads and stores, written through to memory
                                 in large calls (default 1) */
   EMU_OPT_LDS_STAGING = 3,   /* 1 = stage each tile through LDS between load and store (default 0) */
