@@ -1,5 +1,6 @@
-// How one reshard, pack or unpack call is launched, from what it moves: the cache policy of its stores and
-// the most workgroups resident per CU. Host code of its own, so that the rules can be checked without a GPU.
+// How one reshard, pack or unpack call is launched, from what it moves: the cache policy of its stores,
+// the most workgroups resident per CU and the order of the reshard's tiles. Host code of its own, so that the
+// rules can be checked without a GPU.
 #include "emu.h"
 #include "emu_internal.h"
 
@@ -46,7 +47,7 @@ static int resident(uint64_t tile_bytes, uint64_t flight, int least = 2) {
 //    map below, where the front of one to three rounds leaves XCDs idle at its end: three states in rotation, in
 //    blocks / eighths, 2,789 tiles 5.28 / 4.72 us, 3,371 tiles 6.45 / 6.04, 5,321 tiles 9.04 / 8.62, 7,009 tiles 11.05 /
 //    11.03, 10,385 tiles 15.3 / 15.1 (a Merge 15.6 / 15.9), 17,137 tiles 23.5 / 23.7. Tiles at any alignment take longer
-//    than others, and eighths deal them unevenly: blocks there, 7,945 tiles 13.55 / 13.95, 7,636 tiles 12.8 / 13.2.
+//    than others, and eighths deal them unevenly: blocks there, 7,945 tiles 13.55 / 13.95, 8,000 tiles 12.8 / 13.2.
 constexpr uint64_t kThroughBytes = 1ull << 30;  // read and written by one reshard launch
 constexpr uint64_t kBlockTiles = 4 * kXcdCount * kReshardBlock;
 
